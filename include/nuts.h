@@ -67,7 +67,8 @@ enum {
 enum {
     NUTS_PATH_AUTO = 0,
     NUTS_PATH_WAVE = 1,  /* one wavefront per chain, whole tree on device */
-    NUTS_PATH_GRID = 2,  /* one chain over the whole GPU, grid barrier per leapfrog step */
+    NUTS_PATH_GRID = 2,  /* the GPU's compute units shared out to the chains (one chain: all of them),
+                            the rows split over a chain's units, their sums exchanged per leapfrog step */
     NUTS_PATH_BATCH = 3  /* many chains on shared fp32 data: one leapfrog step of every chain
                             per pass, the gradients as a matrix product on the matrix cores */
 };

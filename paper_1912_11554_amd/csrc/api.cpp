@@ -858,36 +858,36 @@ int nuts_sample_data(nuts_handle* h, const nuts_data* d, uint32_t flags, double 
 
     DeviceScope ds(h->device);
     int path = o.path;
+    if (per_chain && (path == NUTS_PATH_GRID || path == NUTS_PATH_BATCH))
+        return fail(h, NUTS_EUNSUPPORTED, "the grid and batch paths run chains on shared data only");
+    GridPlan grid_plan{0, 0, 0};
     if (path == NUTS_PATH_AUTO) {
         // many chains on a large shared fp32 data set: the matrix-core batch;
-        // one wave per chain when there are many chains or the data is small;
-        // the whole device on one chain when the data is large
+        // else the chains side by side on the grid path, each on its share of
+        // the device, unless one wave per chain is expected to be faster
+        // (many small models)
         int kt = 0, tc = 0;
         const bool batchable = !per_chain && d->view.dtype == NUTS_F32 && num_chains >= 16 &&
                                (double)d->view.N * d->view.D >= 262144.0 && batch_shape(d->view.D, &kt, &tc);
-        const bool small = d->view.nb <= 6;  // a few blocks: one wave beats a grid-wide exchange
-        // a lone chain whose data set fits in one group's LDS is faster on
-        // one wave than on a grid-wide exchange per step
         SamplerArgs probe;
         std::memset(&probe, 0, sizeof probe);
         probe.data = d->view;
         probe.max_depth = max_tree_depth;
         probe.num_chains = num_chains;
         probe.sub_merge = sub_merge;
-        const bool resident = wave_path_supports(d->view) && wave_path_resident(probe);
         if (batchable && ensure_batch_layout(h, d) == NUTS_OK &&
-            batch_sampler_supported(d->batch, max_tree_depth, sub_merge, h->num_cu))
+            batch_sampler_supported(d->batch, max_tree_depth, sub_merge, h->num_cu)) {
             path = NUTS_PATH_BATCH;
-        else
-            path = ((per_chain || small || resident || num_chains > 1) && wave_path_supports(d->view))
-                       ? NUTS_PATH_WAVE
-                       : NUTS_PATH_GRID;
+        } else if (wave_path_supports(d->view)) {
+            grid_plan = plan_grid_sampler(d->view, max_tree_depth, sub_merge, num_chains, h->num_cu);
+            path = grid_beats_wave(probe, grid_plan, h->num_cu) ? NUTS_PATH_GRID : NUTS_PATH_WAVE;
+        } else {
+            path = NUTS_PATH_GRID;
+        }
         h->err.clear();
     }
     if (path != NUTS_PATH_WAVE && path != NUTS_PATH_GRID && path != NUTS_PATH_BATCH)
         return fail(h, NUTS_EINVAL, "unknown path %d", path);
-    if ((path == NUTS_PATH_GRID || path == NUTS_PATH_BATCH) && per_chain)
-        return fail(h, NUTS_EUNSUPPORTED, "the grid and batch paths run chains on shared data only");
     if (path == NUTS_PATH_WAVE && !wave_path_supports(d->view))
         return fail(h, NUTS_EUNSUPPORTED, "the one-wave-per-chain path takes D <= 64 (got %d)", d->view.D);
     if (path == NUTS_PATH_BATCH) {
@@ -950,36 +950,36 @@ int nuts_sample_data(nuts_handle* h, const nuts_data* d, uint32_t flags, double 
                             (long long)c0);
         }
     } else {
-        const int groups = grid_sampler_groups(d->view, max_tree_depth, sub_merge, h->num_cu);
-        if (groups == 0)
+        const GridPlan plan = grid_plan.groups
+                                  ? grid_plan
+                                  : plan_grid_sampler(d->view, max_tree_depth, sub_merge, C, h->num_cu);
+        if (plan.groups == 0)
             return fail(h, NUTS_EUNSUPPORTED, "the grid path's tree state (D = %d, depth %d) does not fit a CU's LDS",
                         D, max_tree_depth);
-        const size_t part_bytes = align256((size_t)grid_partial_elems(D, groups) * sizeof(double));
-        const size_t res_bytes = align256((size_t)grid_result_elems(D) * sizeof(double));
-        void* scratch = nullptr;
-        HIP_TRY(h, handle_scratch(h, part_bytes + res_bytes + sizeof(GridSync), &scratch));
-        double* part = (double*)scratch;
-        double* res = (double*)((char*)scratch + part_bytes);
-        GridSync* sync = (GridSync*)((char*)scratch + part_bytes + res_bytes);
-        for (int64_t c = 0; c < C; ++c) {
-            SamplerArgs ac = a;
-            ac.num_chains = 1;
-            ac.chain_offset = c;
-            HIP_TRY(h, launch_sampler_grid(ac, groups, part, res, sync, s, kev && c == 0 ? kev[0] : nullptr));
-            if (kev) HIP_TRY(h, hipEventRecord(kev[1], s));
-            if (c + 1 < C) {
-                // the next chain's launch clears the flag: check this one's first
-                GridSync hs;
-                HIP_TRY(h, hipMemcpyAsync(&hs, sync, sizeof hs, hipMemcpyDeviceToHost, s));
-                HIP_TRY(h, hipStreamSynchronize(s));
-                if (hs.error)
-                    return fail(h, NUTS_EDEVICE, "grid barrier timed out in chain %lld (a group stopped responding)",
-                                (long long)c);
-            }
+        double *part = nullptr, *res = nullptr;
+        GridSync* sync = nullptr;
+        if (plan.groups > 1 || plan.team == 0) {  // else a lone group: nothing is exchanged
+            const size_t part_bytes =
+                align256((size_t)plan.chains * grid_partial_elems(D, plan.groups) * sizeof(double));
+            const size_t res_bytes = align256((size_t)plan.chains * grid_result_elems(plan.groups) * sizeof(double));
+            void* scratch = nullptr;
+            HIP_TRY(h, handle_scratch(h, part_bytes + res_bytes + sizeof(GridSync), &scratch));
+            part = (double*)scratch;
+            res = (double*)((char*)scratch + part_bytes);
+            sync = (GridSync*)((char*)scratch + part_bytes + res_bytes);
         }
-        // the last chain's flag is read with the outputs
-        return rb.finish(h, o, out_samples, out_stats, &sync->error,
-                         "grid barrier timed out in the last chain (a group stopped responding)");
+        // launches of plan.chains chains side by side; the error flag is
+        // cleared by the first and read with the outputs
+        for (int64_t c = 0; c < C; c += plan.chains) {
+            SamplerArgs ac = a;
+            ac.num_chains = std::min<int64_t>(plan.chains, C - c);
+            ac.chain_offset = c;
+            HIP_TRY(h, launch_sampler_grid(ac, plan, part, res, sync, c == 0, s,
+                                           kev && c == 0 ? kev[0] : nullptr));
+            if (kev) HIP_TRY(h, hipEventRecord(kev[1], s));
+        }
+        return rb.finish(h, o, out_samples, out_stats, sync ? &sync->error : nullptr,
+                         "grid barrier timed out (a group stopped responding)");
     }
     return rb.finish(h, o, out_samples, out_stats);
 }

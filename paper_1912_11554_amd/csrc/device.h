@@ -111,6 +111,7 @@ __device__ __noinline__ double momentum_normal(uint64_t seed, uint64_t chain, ui
 enum : int {
     kDppXor1 = 0xB1,        // quad_perm [1, 0, 3, 2]
     kDppXor2 = 0x4E,        // quad_perm [2, 3, 0, 1]
+    kDppXor3 = 0x1B,        // quad_perm [3, 2, 1, 0]
     kDppHalfMirror = 0x141, // lane i <-> 7 - i inside each 8 lanes
     kDppMirror = 0x140,     // lane i <-> 15 - i inside each 16 lanes
     kDppRor8 = 0x128        // lane i <-  (i + 8) mod 16, i.e. i ^ 8

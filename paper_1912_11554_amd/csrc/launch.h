@@ -56,11 +56,12 @@ struct DataView {
 // reads up to cols * S * R <= 16 * 128 elements from a block's start.
 constexpr int64_t kTailElems = 2048;
 
-inline int rows_per_block(const DataView& dv)
+__host__ __device__ inline int block_rows(const DataView& dv)
 {
     const int rpl = (dv.dtype == NUTS_F32 || dv.split == 1) ? 2 : 1;
     return rpl * 64 / dv.split;
 }
+inline int rows_per_block(const DataView& dv) { return block_rows(dv); }
 
 // Width of one partial-sum row: the D columns padded to whole lanes, then
 // one more lane-row whose slot 0 is the loss sum.
@@ -130,30 +131,49 @@ struct SamplerArgs {
 // One wavefront per chain (D <= 64): ceil(C / 4) groups of four waves.
 hipError_t launch_sampler_wave(const SamplerArgs& a, hipStream_t stream);
 bool wave_path_supports(const DataView& dv);
-// The chains' data sets fit in LDS (the resident variant of the wave path).
-bool wave_path_resident(const SamplerArgs& a);
+// Chains per group whose data sets fit in LDS (the resident variant of the wave
+// path; 0: not even one).
+int wave_path_resident(const SamplerArgs& a);
 
-// One chain over the whole device.  `sync` holds the error flag, zeroed by
-// this call; `partials` holds grid_partial_elems(D, groups) doubles and
-// `result` grid_result_elems(D) doubles, both marked empty by this call.
-// The result row of each phase is kept in kGridReplicas copies, kReplicaStride
-// doubles apart (4 KiB + 256 B, so that the copies fall in different memory
-// channels): every controller polls its row once per round trip, and 256 of
-// them on one row queue at the channel that holds it.
+// The grid path: a launch runs a.num_chains chains side by side, each on
+// `groups` workgroups of its own (GridPlan); chains never wait for each other.
+// `partials` holds grid_partial_elems(D, groups) and `result`
+// grid_result_elems(groups) doubles per chain of the launch, all marked empty
+// by this call unless a team runs on one group (it exchanges nothing and takes
+// null pointers).  `sync` holds the error flag; `clear_error` zeroes it first.
+// The result row of each phase is kept in grid_replicas(groups) copies,
+// kReplicaStride doubles apart (4 KiB + 256 B, so that the copies fall in
+// different memory channels): every controller polls its row once per round
+// trip, and 256 of them on one row queue at the channel that holds it.
 constexpr int kGridPhases = 3;
 constexpr int kGridReplicas = 16;
 constexpr int kReplicaStride = 544;  // >= partial_width(D) for D <= 448
-inline int64_t grid_partial_elems(int D, int groups) { return (int64_t)kGridPhases * (D + 1) * groups; }
-inline int64_t grid_result_elems(int) { return (int64_t)kGridPhases * kGridReplicas * kReplicaStride; }
+__host__ __device__ inline int grid_replicas(int groups) { return groups < kGridReplicas ? groups : kGridReplicas; }
+__host__ __device__ inline int64_t grid_partial_elems(int D, int groups)
+{
+    return (int64_t)kGridPhases * (D + 1) * groups;
+}
+__host__ __device__ inline int64_t grid_result_elems(int groups)
+{
+    return (int64_t)kGridPhases * grid_replicas(groups) * kReplicaStride;
+}
 struct GridSync {
     unsigned int error;  // a wait timed out
     unsigned int pad[63];
 };
+struct GridPlan {
+    int groups;  // per chain; 0: the tree state does not fit a CU's LDS
+    int chains;  // per launch
+    int team;    // row tiles a group holds in LDS (sampler_team_kernel), or 0: the rows stream from memory
+};
 // `at_launch` (optional): an event recorded right before the sampler kernel,
 // after the set-up kernel.
-hipError_t launch_sampler_grid(const SamplerArgs& a, int groups, double* partials, double* result,
-                               GridSync* sync, hipStream_t stream, hipEvent_t at_launch = nullptr);
-int grid_sampler_groups(const DataView& dv, int max_depth, int sub_merge, int num_cu);
+hipError_t launch_sampler_grid(const SamplerArgs& a, const GridPlan& plan, double* partials, double* result,
+                               GridSync* sync, bool clear_error, hipStream_t stream, hipEvent_t at_launch = nullptr);
+// Whether the grid path is expected to run these chains faster than the wave
+// path (D <= 64).
+bool grid_beats_wave(const SamplerArgs& a, const GridPlan& plan, int num_cu);
+GridPlan plan_grid_sampler(const DataView& dv, int max_depth, int sub_merge, int64_t num_chains, int num_cu);
 
 // ---------------------------------------------------------------------------
 // Batched chains on shared fp32 data: the potential and gradient of K
@@ -255,16 +275,20 @@ constexpr int kBatchQWidth = 192;
 // Per-dtype kernel entry points (sampler_f32.hip, sampler_f64.hip).
 hipError_t launch_sampler_wave_f32(const SamplerArgs& a, hipStream_t stream);
 hipError_t launch_sampler_wave_f64(const SamplerArgs& a, hipStream_t stream);
-bool wave_resident_f32(const SamplerArgs& a);
-bool wave_resident_f64(const SamplerArgs& a);
+int wave_resident_f32(const SamplerArgs& a);
+int wave_resident_f64(const SamplerArgs& a);
 const void* grid_kernel_f32(const DataView& dv);
 const void* grid_kernel_f64(const DataView& dv);
+const void* team_kernel_f32(int D);
+const void* team_kernel_f64(int D);
 // The same with the optional features compiled in: warmup step-size
 // adaptation, the generalised U-turn criterion (sampler_ext_*.hip).
 hipError_t launch_sampler_wave_ext_f32(const SamplerArgs& a, hipStream_t stream);
 hipError_t launch_sampler_wave_ext_f64(const SamplerArgs& a, hipStream_t stream);
 const void* grid_kernel_ext_f32(const DataView& dv);
 const void* grid_kernel_ext_f64(const DataView& dv);
+const void* team_kernel_ext_f32(int D);
+const void* team_kernel_ext_f64(int D);
 // Whether a launch needs the kernels with the adaptation.
 inline bool sampler_extended(const SamplerArgs& a)
 {
@@ -295,6 +319,7 @@ __host__ __device__ inline int64_t chain_lds_doubles(int D, int max_depth, int s
 __host__ __device__ inline bool grid_edge_nodes(int D) { return D > 128; }
 __host__ __device__ inline bool batch_edge_nodes(int D, bool extended) { return D > 128 && !extended; }
 constexpr int kGridWaves = 12;  // per group: 1 controller + 11 workers (3 waves per SIMD: 168 registers each)
+constexpr int kTeamWaves = 8;   // the same for data held in LDS: 1 controller + 7 workers (2 per SIMD: 256 registers)
 
 // Grid path: every worker keeps the last blocks of its share in LDS for the
 // whole launch (as many as the group's LDS beside the chain's state holds),
@@ -313,6 +338,15 @@ __host__ __device__ inline size_t grid_resident_offset(int D, int max_depth, int
 {
     const size_t b = (size_t)chain_lds_doubles(D, max_depth, sub_merge, grid_edge_nodes(D)) * sizeof(double);
     return (b + 15) & ~(size_t)15;
+}
+
+// Bytes of a row tile in LDS (RowTile): 64 rows of the tile shape's columns
+// (the smallest that holds D <= 64) and their labels.
+inline int team_tile_bytes(int dtype, int D)
+{
+    const int cols = D <= 4 ? 4 : D <= 8 ? 8 : D <= 12 ? 12 : D <= 16 ? 16 : D <= 24 ? 24 : D <= 32 ? 32
+                     : D <= 48 ? 48 : 64;
+    return cols * 64 * (dtype == NUTS_F64 ? 8 : 4) + 64;
 }
 
 // Semi-supervised hidden Markov model (hmm.hip, hmm_ext.hip): symbols w [T]

@@ -116,7 +116,7 @@ __global__ void __launch_bounds__((pot_waves<T, S, CPS>() * kWave))
             a, X, y, D, dv.N, dv.nb, first, (int64_t)G * NW, qv, acc, loss);
 
     double* row = part + wave * width;
-    if constexpr (S <= 8 && CPS == 8) {
+    if constexpr (S <= 8) {
         const double col = finish_pass<CPS, S>(acc, loss);
         if (l < D) row[l] = col;
         if (l == 0) row[loss_slot] = loss;

@@ -468,6 +468,134 @@ __device__ __forceinline__ double finish_pass(double (&acc)[CPS], double& loss)
     return L < CPS * S ? col : 0.0;
 }
 
+// ---------------------------------------------------------------------------
+// Row tiles in LDS (data sets kept there for a whole launch).
+//
+// With S lanes on a row, compute_block evaluates the row's exponential,
+// logarithm and reciprocal in each of the S lanes: about 75 of the 100 vector
+// instructions of an fp64 block at S = 4 do work that a neighbour lane does
+// too.  A tile instead holds 64 rows, one per lane for the row terms: row i of
+// lane group rg (lanes rg * S .. rg * S + S - 1, i < S) is row i * (64 / S) +
+// rg of the tile, its columns k * S + p in lane part p, and lane part p
+// evaluates the terms of its group's row i = p.  Lane part p takes the rows
+// of its group in the order i = p ^ 0, p ^ 1, .. p ^ (S - 1), so that the
+// partial dot products of one row and its residual travel between lanes by
+// fixed exchanges (DPP moves, no selects): the order lives in each lane's
+// LDS address, which keeps a read's 64 lanes on 64 different slots.
+//
+// Element (i, k) of lane L is at (i * CPS + k) * 64 + L, then one label byte a
+// lane (that of the row whose terms it evaluates).  Columns past D - 1 and
+// rows past N hold zeros.
+template <typename T, int S, int CPS>
+struct RowTile {
+    static constexpr int kRows = 64;
+    static constexpr int kXBytes = S * CPS * 64 * (int)sizeof(T);
+    static constexpr int kBytes = kXBytes + 64;  // a multiple of 16
+
+    // Fill from rows row0 .. row0 + 63 of a data set in column blocks of R
+    // rows (rows past N are taken as zero).
+    __device__ static void fill(char* tile, const T* __restrict__ X, const uint8_t* __restrict__ y, int D, int64_t N,
+                                int R, int64_t row0)
+    {
+        const int L = lane();
+        const int p = L & (S - 1);
+        T* x = reinterpret_cast<T*>(tile);
+#pragma unroll 1
+        for (int i = 0; i < S; ++i) {
+            const int64_t row = row0 + i * (64 / S) + L / S;
+            const int64_t b = row / R;
+            const T* src = X + b * D * R + (row - b * R);
+#pragma unroll 1
+            for (int k = 0; k < CPS; ++k) {
+                const int c = k * S + p;
+                T v = T(0);
+                if (row < N && c < D) v = src[(int64_t)c * R];
+                x[(i * CPS + k) * 64 + L] = v;
+            }
+        }
+        const int64_t own = row0 + p * (64 / S) + L / S;
+        reinterpret_cast<uint8_t*>(tile + kXBytes)[L] = own < N ? y[own] : (uint8_t)0;
+    }
+};
+
+// The value of lane (this lane ^ M), M < 8: quad permutes, and the mirror of 8
+// lanes (lane ^ 7) followed by one.
+template <int M>
+__device__ __forceinline__ double octet_move(double v)
+{
+    static_assert(M >= 0 && M < 8, "inside 8 lanes");
+    if constexpr (M >= 4) return octet_move<M ^ 7>(dpp_f64<kDppHalfMirror>(v));
+    else if constexpr (M == 1) return dpp_f64<kDppXor1>(v);
+    else if constexpr (M == 2) return dpp_f64<kDppXor2>(v);
+    else if constexpr (M == 3) return dpp_f64<kDppXor3>(v);
+    else return v;
+}
+
+// Rows of one tile: qv[k] holds q[k * S + L % S] (zero for columns >= D);
+// rows at or past rows_left add nothing.
+template <typename T, int S, int CPS>
+__device__ __forceinline__ void compute_tile(const char* tile, int64_t rows_left, const double (&qv)[CPS],
+                                             double (&acc)[CPS], double& loss)
+{
+    static_assert(S == 1 || S == 2 || S == 4 || S == 8, "lanes of one DPP octet");
+    const int L = lane();
+    const int p = L & (S - 1);
+    const T* x = reinterpret_cast<const T*>(tile) + L;
+    const uint8_t label = reinterpret_cast<const uint8_t*>(tile + RowTile<T, S, CPS>::kXBytes)[L];
+    double e[S];
+#pragma unroll
+    for (int m = 0; m < S; ++m) {
+        const T* xm = x + (p ^ m) * (CPS * 64);
+        double s = (double)xm[0] * qv[0];
+#pragma unroll
+        for (int k = 1; k < CPS; ++k) s = fma((double)xm[k * 64], qv[k], s);
+        e[m] = s;
+    }
+    // lane part p's row is the row p ^ m of its group's lane p ^ m, slot m
+    double eta = e[0];
+    if constexpr (S == 8) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) e[m] += dpp_f64<kDppHalfMirror>(e[7 - m]);
+        eta = e[0];
+    }
+    if constexpr (S >= 2) eta += octet_move<1>(e[1]);
+    if constexpr (S >= 4) eta += octet_move<2>(e[2]) + octet_move<3>(e[3]);
+    const RowTerms rt = logistic_row_t<T>(eta, label != 0);
+    const bool valid = p * (64 / S) + L / S < rows_left;
+    const double r = valid ? rt.resid : 0.0;
+    loss += valid ? rt.loss : 0.0;
+    // past 32 doubles of x a lane the elements are read again
+    if constexpr (S * CPS > 32) asm volatile("" ::: "memory");
+    double rh = r;
+    if constexpr (S == 8) rh = dpp_f64<kDppHalfMirror>(r);
+#pragma unroll
+    for (int m = 0; m < S; ++m) {
+        const T* xm = x + (p ^ m) * (CPS * 64);
+        double rm = r;
+        if (m == 1) rm = octet_move<1>(r);
+        if (m == 2) rm = octet_move<2>(r);
+        if (m == 3) rm = octet_move<3>(r);
+        if (m == 4) rm = octet_move<3>(rh);
+        if (m == 5) rm = octet_move<2>(rh);
+        if (m == 6) rm = octet_move<1>(rh);
+        if (m == 7) rm = rh;
+#pragma unroll
+        for (int k = 0; k < CPS; ++k) acc[k] = fma(rm, (double)xm[k * 64], acc[k]);
+    }
+}
+
+// finish_pass for a CPS that need not be a power of two.
+template <int CPS, int S>
+__device__ __forceinline__ double finish_tiles(const double (&acc)[CPS], double& loss)
+{
+    constexpr int P = CPS <= 4 ? 4 : 8;
+    static_assert(CPS <= P, "at most 8 slots a lane");
+    double a[P];
+#pragma unroll
+    for (int k = 0; k < P; ++k) a[k] = k < CPS ? acc[k < CPS ? k : 0] : 0.0;
+    return finish_pass<P, S>(a, loss);
+}
+
 // Load q (lane-per-dimension, zero past D) into the per-lane column order.
 template <int CPS, int S>
 __device__ __forceinline__ void spread_position(double q, double (&qv)[CPS])
@@ -477,7 +605,10 @@ __device__ __forceinline__ void spread_position(double q, double (&qv)[CPS])
     for (int k = 0; k < CPS; ++k) qv[k] = __shfl(q, (k * S + p) & (kWave - 1));
 }
 
-// The same from a position vector in LDS (zero past D).
+// The same from a position vector in memory (zero past D).  With one lane per
+// row every lane needs the same CPS components: they go to scalar registers
+// (a fused multiply-add takes one as an operand), which leaves 2 CPS vector
+// registers a lane to the data pass.
 template <int CPS, int S>
 __device__ __forceinline__ void spread_position_lds(const double* q, int D, double (&qv)[CPS])
 {
@@ -486,6 +617,7 @@ __device__ __forceinline__ void spread_position_lds(const double* q, int D, doub
     for (int k = 0; k < CPS; ++k) {
         const int c = k * S + p;
         qv[k] = c < D ? q[c] : 0.0;
+        if constexpr (S == 1) qv[k] = readlane_f64(qv[k], 0);
     }
 }
 

@@ -9,7 +9,7 @@ hipError_t launch_sampler_wave_f64(const SamplerArgs& a, hipStream_t stream)
     return sampler::wave_launch_split<double, false>(a, stream);
 }
 
-bool wave_resident_f64(const SamplerArgs& a)
+int wave_resident_f64(const SamplerArgs& a)
 {
     return sampler::wave_resident_split<double>(a);
 }

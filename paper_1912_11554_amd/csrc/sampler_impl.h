@@ -13,9 +13,10 @@
 // Two evaluators supply U and grad U at a position:
 //   WaveEval -- one wave streams its chain's data set (small data; one wave
 //               per chain, thousands of chains per launch; D <= 64);
-//   GridEval -- one chain on the whole device.  In every group, wave 0 is the
-//               controller (it runs the tree logic) and the other waves are
-//               workers (they stream a slice of the rows).  Group partials
+//   GridEval -- each chain on its share of the device's workgroups (one chain:
+//               all of them).  In every group, wave 0 is the controller (it
+//               runs the tree logic) and the other waves are workers (they
+//               take a slice of the rows: streamed, or held in LDS).  Group partials
 //               meet in a grid-wide exchange where each column has an owner
 //               group that adds its partials in a fixed order.  Controller and workers run the same collective
 //               with the same workgroup barriers; only the workers' copy
@@ -234,9 +235,11 @@ struct GridCtx {
     const uint8_t* y;
     int64_t N, nb;
     int D;
-    int groups;
+    int groups;        // of this chain
+    int g;             // this group's index among them
+    int replicas;      // grid_replicas(groups)
     double* partials;  // [kGridPhases][D + 1][groups]
-    double* result;    // [kGridPhases][kGridReplicas][kReplicaStride], W used of each row
+    double* result;    // [kGridPhases][replicas][kReplicaStride], W used of each row
     GridSync* sync;
 };
 
@@ -331,11 +334,12 @@ struct WaveShare {
     ResidentBlocks res;
 };
 
-__device__ inline WaveShare grid_wave_share(int64_t nb, int groups, int wave, int resident, const char* res_base)
+__device__ inline WaveShare grid_wave_share(int64_t nb, int groups, int g, int wave, int resident,
+                                            const char* res_base)
 {
     WaveShare w;
     w.stride = (int64_t)groups * (kGridWaves - 1);
-    w.first = (int64_t)blockIdx.x * (kGridWaves - 1) + (wave - 1);
+    w.first = (int64_t)g * (kGridWaves - 1) + (wave - 1);
     const int64_t count = w.first < nb ? (nb - 1 - w.first) / w.stride + 1 : 0;
     const int nres = count >= 2 ? (int)(count - 1 < resident ? count - 1 : resident) : 0;
     w.nb_mem = count > 0 ? w.first + (count - nres - 1) * w.stride + 1 : nb;
@@ -380,7 +384,7 @@ __device__ __forceinline__ int result_pos(int ci, int D, int DPL) { return ci < 
 // lanes in butterfly order), store the column's result slot in every copy of
 // the result row and empty the same slots of the previous phase.  The
 // controller of group g waits for the result slots of its lanes in copy
-// g mod kGridReplicas.  Emptying is safe: a group's partial of step s is written
+// g mod replicas.  Emptying is safe: a group's partial of step s is written
 // after its controller read all of step s - 1's results, and the next write
 // of an emptied slot comes only after the worker that emptied it has waited
 // for its own stores (s_waitcnt at its next step, before it stores the next
@@ -405,7 +409,7 @@ __device__ int grid_begin(const GridCtx& c, GridShared<DPL, NW>& sh, const doubl
     const int cmd = sh.cmd;
     *gen_out = sh.gen;
     if (cmd == kCmdExit) return cmd;
-    if (WORKER) {
+    if constexpr (WORKER) {
         const int D = c.D;
         double qv[CPS];
         spread_position_lds<CPS, S>(sh.qbuf, D, qv);
@@ -422,7 +426,7 @@ __device__ int grid_begin(const GridCtx& c, GridShared<DPL, NW>& sh, const doubl
             stream_blocks<T, CPS, S, kGridPipe<T>, kGridPipe<T>, true, true>((const T*)c.X, c.y, D, c.N, ws.nb_mem,
                                                                             ws.first, ws.stride, qv, acc, loss,
                                                                             &sh.stop, *gen_out, ws.res);
-        if constexpr (S <= 8 && CPS == 8) {
+        if constexpr (S <= 8) {
             const double col = finish_pass<CPS, S>(acc, loss);
             if (l < D) sh.red[wave][l] = col;
             if (l == 0) sh.red[wave][64 * DPL] = loss;
@@ -433,7 +437,8 @@ __device__ int grid_begin(const GridCtx& c, GridShared<DPL, NW>& sh, const doubl
     return cmd;
 }
 
-template <typename T, int S, int CPS, int DPL, int NW, bool WORKER>
+// LONE_OK: the chain may run on a single group, which exchanges nothing.
+template <typename T, int S, int CPS, int DPL, int NW, bool WORKER, bool LONE_OK = false>
 __device__ bool grid_end(const GridCtx& c, GridShared<DPL, NW>& sh, unsigned long long step, int gen, bool stop,
                          double (&out_r)[DPL + 1], bool* aborted)
 {
@@ -449,7 +454,30 @@ __device__ bool grid_end(const GridCtx& c, GridShared<DPL, NW>& sh, unsigned lon
     const int D = c.D;
     const int used = D + 1;
     const int G = c.groups;
-    const int g = blockIdx.x;
+    const int g = c.g;
+    if (LONE_OK && G == 1) {
+        // one group for the chain: the controller adds the workers' rows, in
+        // wave order, straight from LDS (the workers write them again only
+        // after the next collective's first barrier)
+        if constexpr (!WORKER) {
+#pragma unroll
+            for (int m = 0; m <= DPL; ++m) {
+                double s = 0.0;
+                const bool used_slot = m < DPL ? l + 64 * m < D : l == 0;
+#pragma unroll
+                for (int w = 1; w < NW; ++w) s += sh.red[w][l + 64 * m];
+                out_r[m] = used_slot ? s : 0.0;
+            }
+            // the loss where the result row would hold it
+            const int lp = loss_pos(D, DPL);
+            const double loss = readlane_f64(out_r[DPL], 0);
+#pragma unroll
+            for (int m = 0; m < DPL; ++m)
+                if (l + 64 * m == lp) out_r[m] = loss;
+            *aborted = false;
+        }
+        return true;
+    }
     double* part = c.partials + (int64_t)ph * used * G;
 
     if (WORKER && wave == 1) {
@@ -490,11 +518,11 @@ __device__ bool grid_end(const GridCtx& c, GridShared<DPL, NW>& sh, unsigned lon
                 double s = 0.0;
                 for (int t = l; t < G; t += kWave) s += sh.red_flat[jc * G + t];
                 s = wave_sum(s);  // the same bits in every lane
-                if (l < kGridReplicas) {
+                if (l < c.replicas) {
                     const int pos = result_pos(ci, D, DPL);
                     const int prev = (ph + kGridPhases - 1) % kGridPhases;
-                    store_shared(&c.result[(ph * kGridReplicas + l) * kReplicaStride + pos], s);
-                    empty_slot(&c.result[(prev * kGridReplicas + l) * kReplicaStride + pos]);
+                    store_shared(&c.result[(ph * c.replicas + l) * kReplicaStride + pos], s);
+                    empty_slot(&c.result[(prev * c.replicas + l) * kReplicaStride + pos]);
                 }
             }
         }
@@ -502,7 +530,7 @@ __device__ bool grid_end(const GridCtx& c, GridShared<DPL, NW>& sh, unsigned lon
     if (WORKER) return true;
 
     // controller: wait for this lane's result slots, all at once
-    const double* row = &c.result[(ph * kGridReplicas + g % kGridReplicas) * kReplicaStride];
+    const double* row = &c.result[(ph * c.replicas + g % c.replicas) * kReplicaStride];
     const int lp = loss_pos(D, DPL);
     unsigned long long bits[DPL + 1];
 #pragma unroll
@@ -543,7 +571,7 @@ __device__ bool grid_end(const GridCtx& c, GridShared<DPL, NW>& sh, unsigned lon
 // (begin) and collect it later (end), so that run_chain hands the workers the
 // next leapfrog position before it does the tree logic of the current leaf;
 // cancel() calls a started evaluation off.
-template <typename T, int S, int CPS, int DPL, int NW>
+template <typename T, int S, int CPS, int DPL, int NW, bool LONE_OK = false>
 struct GridEval {
     static constexpr bool kSpeculative = true;
     static constexpr bool kNodesInLds = DPL >= 3;  // the edge and proposal nodes in LDS (see EdgeNodes)
@@ -555,7 +583,7 @@ struct GridEval {
     bool abort;
 
     __device__ bool s_writer() const { return true; }  // only the controller runs the chain
-    __device__ bool out_writer() const { return blockIdx.x == 0; }
+    __device__ bool out_writer() const { return c.g == 0; }
     __device__ bool aborted() const { return abort; }
 
     // A called-off collective's second barrier, which the workers wait at
@@ -585,7 +613,7 @@ struct GridEval {
     {
         double r[DPL + 1];
         bool ab = false;
-        grid_end<T, S, CPS, DPL, NW, false>(c, *sh, step, gen, false, r, &ab);
+        grid_end<T, S, CPS, DPL, NW, false, LONE_OK>(c, *sh, step, gen, false, r, &ab);
         abort = ab;
         step++;
         double pr = 0.0;
@@ -1355,15 +1383,21 @@ __global__ void __launch_bounds__(kGridWaves * kWave, 1) sampler_grid_kernel(Sam
                   "the host sizes resident blocks as the kernel lays them out");
     extern __shared__ double lds[];
     __shared__ GridShared<DPL, kGridWaves> sh;
+    // groups [chain * groups, (chain + 1) * groups) run chain `chain` of the
+    // launch; chains never wait for each other
+    const int64_t chain = blockIdx.x / groups;
     GridCtx c;
-    c.X = A.data.X;
-    c.y = A.data.y;
     c.N = A.data.N;
     c.nb = A.data.nb;
     c.D = A.data.D;
+    const int64_t rows = A.per_chain_data ? (A.chain_offset + chain) * c.nb * BlockShape<T, S>::R : 0;
+    c.X = (const T*)A.data.X + rows * c.D;
+    c.y = A.data.y + rows;
     c.groups = groups;
-    c.partials = partials;
-    c.result = result;
+    c.g = (int)(blockIdx.x % groups);
+    c.replicas = grid_replicas(groups);
+    c.partials = partials + chain * grid_partial_elems(c.D, groups);
+    c.result = result + chain * grid_result_elems(groups);
     c.sync = sync;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     if (wave == 0) {
@@ -1377,7 +1411,7 @@ __global__ void __launch_bounds__(kGridWaves * kWave, 1) sampler_grid_kernel(Sam
         ev.step = 0;
         ev.gen = 0;
         ev.abort = false;
-        run_chain<DPL, EXT>(A, ev, 0, lds);
+        run_chain<DPL, EXT>(A, ev, chain, lds);
         ev.finish();
     } else {
         unsigned long long step = 0;
@@ -1393,7 +1427,7 @@ __global__ void __launch_bounds__(kGridWaves * kWave, 1) sampler_grid_kernel(Sam
         using LB = LdsBlock<T, CPS, S>;
         char* res_base = reinterpret_cast<char*>(lds) + grid_resident_offset(c.D, A.max_depth, A.sub_merge) +
                          (size_t)(wave - 1) * resident * LB::kBytes;
-        const WaveShare share = grid_wave_share(c.nb, groups, wave, resident, res_base);
+        const WaveShare share = grid_wave_share(c.nb, groups, c.g, wave, resident, res_base);
         // the resident blocks, loaded once
 #pragma unroll 1
         for (int r = 0; r < share.res.count; ++r) {
@@ -1418,6 +1452,115 @@ __global__ void __launch_bounds__(kGridWaves * kWave, 1) sampler_grid_kernel(Sam
             if (grid_end<T, S, CPS, DPL, kGridWaves, true>(c, sh, step, gen, false, r, &ab)) step++;
         }
     }
+}
+
+// The grid path for data that fits in the LDS of the chain's groups, D <= 64:
+// group g of the chain holds the tiles (RowTile) g, g + groups, .. of its rows
+// in LDS from the start of the launch and its workers take them in turn, so
+// an evaluation reads no memory but the exchange's slots, and with one group a
+// chain not even those.  Controller, command barriers, speculation and
+// exchange are those of sampler_grid_kernel.
+//
+// Bound: the latency of one leapfrog step (position to the workers, one to a
+// few tiles each, reduction over the wave, sums back, tree step of the next
+// leaf overlapped).  Eight waves, so that a wave has 256 registers: with
+// twelve (168) the controller and the wide tiles spilled, and a reload from
+// scratch memory costs a step up to a microsecond.  Measured, microseconds an
+// evaluation against the path these chains took before (one wave a chain):
+// one chain on 1,000 x 11 fp64 2.8 from 6.3, on 4,000 x 50 fp64 5.1 from 222;
+// four chains on 20,000 x 25 fp64 5.3 from 1,056; 256 models of 824 x 20 fp32
+// 2.7 from 9.7.
+template <typename T, int S, int CPS, bool EXT>
+__global__ void __launch_bounds__(kTeamWaves * kWave, 1) sampler_team_kernel(SamplerArgs A, int groups,
+                                                                            double* partials, double* result,
+                                                                            GridSync* sync)
+{
+    using Tile = RowTile<T, S, CPS>;
+    extern __shared__ double lds[];
+    __shared__ GridShared<1, kTeamWaves> sh;
+    const int64_t chain = blockIdx.x / groups;
+    const int D = A.data.D;
+    GridCtx c;
+    c.N = A.data.N;
+    c.nb = A.data.nb;
+    c.D = D;
+    c.X = nullptr;
+    c.y = nullptr;
+    c.groups = groups;
+    c.g = (int)(blockIdx.x % groups);
+    c.replicas = grid_replicas(groups);
+    c.partials = partials + chain * grid_partial_elems(D, groups);
+    c.result = result + chain * grid_result_elems(groups);
+    c.sync = sync;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (wave == 0) {
+        // published by the first collective's barrier
+        if (lane() == 0) __hip_atomic_store(&sh.stop, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        GridEval<T, S, CPS, 1, kTeamWaves, true> ev;
+        ev.c = c;
+        ev.sh = &sh;
+        ev.inv_s2 = 1.0 / (A.prior_scale * A.prior_scale);
+        ev.prior_const = (double)D * (log(A.prior_scale) + kHalfLog2Pi);
+        ev.step = 0;
+        ev.gen = 0;
+        ev.abort = false;
+        run_chain<1, EXT>(A, ev, chain, lds);
+        ev.finish();
+    } else {
+        const int l = lane();
+        char* tiles = reinterpret_cast<char*>(lds) + grid_resident_offset(D, A.max_depth, EXT ? A.sub_merge : 0);
+        const int64_t nt = (c.N + Tile::kRows - 1) / Tile::kRows;
+        const int count = (int)((nt - 1 - c.g) / groups + 1);  // tiles of the group
+        {
+            const int R = block_rows(A.data);
+            const int64_t row_base = A.per_chain_data ? (A.chain_offset + chain) * c.nb * R : 0;
+            const T* X = (const T*)A.data.X + row_base * D;
+            const uint8_t* y = A.data.y + row_base;
+#pragma unroll 1
+            for (int t = wave - 1; t < count; t += kTeamWaves - 1)
+                Tile::fill(tiles + (size_t)t * Tile::kBytes, X, y, D, c.N, R,
+                           (c.g + (int64_t)t * groups) * Tile::kRows);
+        }
+        unsigned long long step = 0;
+        double q[1] = {0.0}, r[2];
+        for (;;) {
+            bool ab;
+            int gen = 0;
+            // (the collective's first barrier; the pass itself is below)
+            if (grid_begin<T, S, CPS, 1, kTeamWaves, false>(c, sh, q, 0, 0, &gen) == kCmdExit) break;
+            double qv[CPS];
+            spread_position_lds<CPS, S>(sh.qbuf, D, qv);
+            double acc[CPS];
+#pragma unroll
+            for (int k = 0; k < CPS; ++k) acc[k] = 0.0;
+            double loss = 0.0;
+#pragma unroll 1
+            for (int t = wave - 1; t < count; t += kTeamWaves - 1) {
+                if (uni(stop_requested<true>(&sh.stop, gen))) break;
+                compute_tile<T, S, CPS>(tiles + (size_t)t * Tile::kBytes,
+                                        c.N - (c.g + (int64_t)t * groups) * Tile::kRows, qv, acc, loss);
+            }
+            const double col = finish_tiles<CPS, S>(acc, loss);
+            if (l < D) sh.red[wave][l] = col;
+            if (l == 0) sh.red[wave][64] = loss;
+            if (grid_end<T, S, CPS, 1, kTeamWaves, true, true>(c, sh, step, gen, false, r, &ab)) step++;
+        }
+    }
+}
+
+// Tile shape for D <= 64 columns: S lanes a row, CPS slots a lane, the
+// smallest S CPS of the instantiated shapes that holds D.
+template <typename T, bool EXT>
+const void* team_kernel_for(int D)
+{
+    if (D <= 4) return (const void*)sampler_team_kernel<T, 1, 4, EXT>;
+    if (D <= 8) return (const void*)sampler_team_kernel<T, 1, 8, EXT>;
+    if (D <= 12) return (const void*)sampler_team_kernel<T, 2, 6, EXT>;
+    if (D <= 16) return (const void*)sampler_team_kernel<T, 2, 8, EXT>;
+    if (D <= 24) return (const void*)sampler_team_kernel<T, 4, 6, EXT>;
+    if (D <= 32) return (const void*)sampler_team_kernel<T, 4, 8, EXT>;
+    if (D <= 48) return (const void*)sampler_team_kernel<T, 8, 6, EXT>;
+    return (const void*)sampler_team_kernel<T, 8, 8, EXT>;
 }
 
 // Kernel for a data shape (S, CPS, DPL as pass_shape gives them).
@@ -1478,16 +1621,17 @@ hipError_t wave_launch(const SamplerArgs& a, hipStream_t stream)
     return hipGetLastError();
 }
 
-// Whether the resident variant takes this shape.
+// Chains per group of the resident variant for this shape (0: it does not
+// take it).
 template <typename T>
-bool wave_resident_split(const SamplerArgs& a)
+int wave_resident_split(const SamplerArgs& a)
 {
     if (a.data.split == 1) {
-        if (a.data.cols == 16) return resident_chains_per_group<T, 1, 16>(a) > 0;
-        return resident_chains_per_group<T, 1, 8>(a) > 0;
+        if (a.data.cols == 16) return resident_chains_per_group<T, 1, 16>(a);
+        return resident_chains_per_group<T, 1, 8>(a);
     }
-    if (a.data.split == 4) return resident_chains_per_group<T, 4, 8>(a) > 0;
-    return resident_chains_per_group<T, 8, 8>(a) > 0;
+    if (a.data.split == 4) return resident_chains_per_group<T, 4, 8>(a);
+    return resident_chains_per_group<T, 8, 8>(a);
 }
 
 template <typename T, bool EXT>
