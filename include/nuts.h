@@ -161,8 +161,9 @@ int nuts_data_potential_grad_noalloc(nuts_handle* h, const nuts_data* d, double 
 int nuts_data_potential_grad_batched(nuts_handle* h, const nuts_data* d, double prior_scale,
                                      const double* W, int64_t K, double* out_U, double* out_grad);
 
-/* One-shot form of the above for a single position w [D]: lays out X and y,
- * evaluates, releases.  N = 0 is allowed (the prior alone). */
+/* One-shot form of the above for a single position w [D]: evaluates on X and
+ * y as they are, without a device layout of them.  The outputs are left alone
+ * when a label is refused.  N = 0 is allowed (the prior alone). */
 int nuts_potential_grad(nuts_handle* h, const void* X, const uint8_t* y, int64_t N, int64_t D,
                         int dtype, double prior_scale, const double* w, double* out_U,
                         double* out_grad);

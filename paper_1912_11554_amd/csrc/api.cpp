@@ -284,6 +284,30 @@ struct DeviceScope {
     }
 };
 
+// Check a data set's arguments and give the shape of its device layout (the
+// view's pointers stay null).
+int check_data(nuts_handle* h, const void* X, const uint8_t* y, int64_t N, int64_t D, int dtype, int64_t num_datasets,
+               DataView* view)
+{
+    if (dtype != NUTS_F64 && dtype != NUTS_F32) return fail(h, NUTS_EINVAL, "dtype must be NUTS_F64 or NUTS_F32");
+    if (N < 0) return fail(h, NUTS_EINVAL, "N must be >= 0 (got %lld)", (long long)N);
+    if (D < 1) return fail(h, NUTS_EINVAL, "D must be >= 1 (got %lld)", (long long)D);
+    if (D > kMaxDim)
+        return fail(h, NUTS_EUNSUPPORTED, "D = %lld exceeds the %d columns the kernels support", (long long)D, kMaxDim);
+    if (num_datasets < 1) return fail(h, NUTS_EINVAL, "num_datasets must be >= 1");
+    if (N > 0 && (!X || !y)) return fail(h, NUTS_EINVAL, "X and y must be non-NULL when N > 0");
+    view->N = N;
+    view->D = (int)D;
+    view->dtype = dtype;
+    const PassShape shape = pass_shape((int)D);
+    view->split = shape.split;
+    view->cols = shape.cols;
+    const int R = rows_per_block(*view);
+    view->nb = (N + R - 1) / R;
+    view->nds = num_datasets;
+    return NUTS_OK;
+}
+
 // Arguments every sampling entry point shares.
 int check_run(nuts_handle* h, uint32_t flags, uint32_t allowed, const nuts_sample_opts& o, double step_size,
               int max_tree_depth, int64_t num_warmup, int64_t num_samples, int64_t num_chains,
@@ -517,26 +541,15 @@ int nuts_data_create(nuts_handle* h, const void* X, const uint8_t* y, int64_t N,
     h->err.clear();
     if (!out) return fail(h, NUTS_EINVAL, "nuts_data_create: out is NULL");
     *out = nullptr;
-    if (dtype != NUTS_F64 && dtype != NUTS_F32) return fail(h, NUTS_EINVAL, "dtype must be NUTS_F64 or NUTS_F32");
-    if (N < 0) return fail(h, NUTS_EINVAL, "N must be >= 0 (got %lld)", (long long)N);
-    if (D < 1) return fail(h, NUTS_EINVAL, "D must be >= 1 (got %lld)", (long long)D);
-    if (D > kMaxDim)
-        return fail(h, NUTS_EUNSUPPORTED, "D = %lld exceeds the %d columns the kernels support", (long long)D, kMaxDim);
-    if (num_datasets < 1) return fail(h, NUTS_EINVAL, "num_datasets must be >= 1");
-    if (N > 0 && (!X || !y)) return fail(h, NUTS_EINVAL, "X and y must be non-NULL when N > 0");
+    DataView view{};
+    const int checked = check_data(h, X, y, N, D, dtype, num_datasets, &view);
+    if (checked != NUTS_OK) return checked;
 
     DeviceScope ds(h->device);
     nuts_data* d = new (std::nothrow) nuts_data();
     if (!d) return fail(h, NUTS_ENOMEM, "out of host memory");
-    d->view.N = N;
-    d->view.D = (int)D;
-    d->view.dtype = dtype;
-    const PassShape shape = pass_shape((int)D);
-    d->view.split = shape.split;
-    d->view.cols = shape.cols;
+    d->view = view;
     const int R = rows_per_block(d->view);
-    d->view.nb = (N + R - 1) / R;
-    d->view.nds = num_datasets;
     const size_t es = elem_size(dtype);
     const size_t xblk = ((size_t)d->view.nb * D * R * num_datasets + (size_t)kTailElems) * es;
     const size_t yblk = (size_t)d->view.nb * R * num_datasets;
@@ -819,12 +832,52 @@ int nuts_data_posterior_predictive(nuts_handle* h, const nuts_data* d, const dou
 int nuts_potential_grad(nuts_handle* h, const void* X, const uint8_t* y, int64_t N, int64_t D, int dtype,
                         double prior_scale, const double* w, double* out_U, double* out_grad)
 {
-    nuts_data* d = nullptr;
-    int rc = nuts_data_create(h, X, y, N, D, dtype, 1, &d);
+    if (N == 0) {  // the prior alone
+        nuts_data* d = nullptr;
+        int rc = nuts_data_create(h, X, y, N, D, dtype, 1, &d);
+        if (rc != NUTS_OK) return rc;
+        rc = nuts_data_potential_grad(h, d, prior_scale, w, 1, out_U, out_grad);
+        nuts_data_free(h, d);
+        return rc;
+    }
+    if (!h) return NUTS_EINVAL;
+    h->err.clear();
+    DataView shape{};
+    int rc = check_data(h, X, y, N, D, dtype, 1, &shape);
     if (rc != NUTS_OK) return rc;
-    rc = nuts_data_potential_grad(h, d, prior_scale, w, 1, out_U, out_grad);
-    nuts_data_free(h, d);
-    return rc;
+    if (!w || !out_U || !out_grad) return fail(h, NUTS_EINVAL, "W, out_U and out_grad must be non-NULL");
+    if (!finite_pos(prior_scale)) return fail(h, NUTS_EINVAL, "prior_scale must be finite and > 0");
+    DeviceScope ds(h->device);
+    DevBuf xs, ys;
+    const void *Xd = nullptr, *yd = nullptr;
+    HIP_TRY(h, stage_in(X, (size_t)N * D * elem_size(dtype), xs, &Xd, h->stream));
+    HIP_TRY(h, stage_in(y, (size_t)N, ys, &yd, h->stream));
+    PositionArg wa;
+    wa.device = is_device_ptr(w) ? w : nullptr;
+    if (!wa.device) std::memcpy(wa.host, w, (size_t)D * 8);
+    const PotentialPlan plan = plan_potential(shape, 1, h->num_cu);
+    double* part = nullptr;
+    HIP_TRY(h, potential_slots(h, (size_t)plan.groups_per_item * plan.width * sizeof(double), &part));
+    // the kernel writes U, grad U and the label check straight to pinned host
+    // memory; the caller's outputs are written once the labels are known to
+    // be good
+    void* pin = nullptr;
+    HIP_TRY(h, handle_pinned(h, (size_t)(D + 2) * 8, &pin));
+    double* U = (double*)pin;
+    double* g = U + 1;
+    unsigned int* bad = (unsigned int*)(g + D);
+    *bad = 0u;
+    HIP_TRY(h, launch_potential_rows(wa, Xd, (const uint8_t*)yd, shape, prior_scale, plan, part, U, g, bad, h->stream));
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    if (*bad) return fail(h, NUTS_EINVAL, "y holds a value other than 0 or 1");
+    const auto put = [&](double* dst, const double* src, size_t n) {
+        if (is_device_ptr(dst)) return hipMemcpy(dst, src, n * 8, hipMemcpyHostToDevice);
+        std::memcpy(dst, src, n * 8);
+        return hipSuccess;
+    };
+    HIP_TRY(h, put(out_U, U, 1));
+    HIP_TRY(h, put(out_grad, g, (size_t)D));
+    return NUTS_OK;
 }
 
 int nuts_sample_data(nuts_handle* h, const nuts_data* d, uint32_t flags, double prior_scale, double step_size,

@@ -88,6 +88,19 @@ PotentialPlan plan_potential(const DataView& dv, int64_t K, int num_cu);
 hipError_t launch_potential_grad(const DataView& dv, double prior_scale, const double* W, int64_t K,
                                  const PotentialPlan& plan, double* partials, double* out_U, double* out_grad,
                                  hipStream_t stream);
+// One position w on N rows of row-major X [N][D] and labels y, both on the
+// device, each read once (shape: the DataView such data would have, its
+// pointers unused; plan: plan_potential's for one position).  The position is
+// a device pointer or travels in the kernel's arguments; out_U, out_grad and
+// bad_label may be pinned host memory.  *bad_label is set to 1 if a label is
+// neither 0 nor 1 (the outputs then mean nothing), else left alone.
+struct PositionArg {
+    const double* device;  // or null: `host` holds it
+    double host[kMaxDim];
+};
+hipError_t launch_potential_rows(const PositionArg& wa, const void* X, const uint8_t* y, const DataView& shape,
+                                 double prior_scale, const PotentialPlan& plan, double* partials, double* out_U,
+                                 double* out_grad, unsigned int* bad_label, hipStream_t stream);
 // Mark n partial-sum slots empty (a kernel on `stream`).
 hipError_t mark_partials_empty(double* p, int64_t n, hipStream_t stream);
 

@@ -77,6 +77,123 @@ __global__ void __launch_bounds__(256) fill_empty_kernel(unsigned long long* __r
         p[i] = kEmptyPartial;
 }
 
+// The sums over the G groups of one position, after every wave of the group has
+// its column sums in row `wave` of part (columns 0..D-1, the loss at
+// loss_slot): the group's partial of each used column goes to row g of the
+// position's slots `item`, and the groups that own a tile of columns add the
+// rows and write U and grad U.  Wk is the position.
+template <int NW>
+__device__ __forceinline__ void sum_groups(double* part, int* failed, const double* Wk, int D, int G, int g, int width,
+                                           double* item, double prior_scale, double* out_U, double* out_grad)
+{
+    const int l = lane();
+    const int wave = threadIdx.x / kWave;
+    const int loss_slot = width - 64;
+    if (threadIdx.x == 0) *failed = 0;
+    __syncthreads();  // per-wave sums in LDS
+    // Row g of the item's slots (at item + g * width) holds the group's
+    // partial of each used column: columns 0..D-1, the loss at D, then zeros
+    // up to a whole number of 128-byte lines, so that every store and every
+    // read between groups moves whole lines (a partial-line write to HBM is
+    // a read-modify-write, and those slowed the other groups' streams).
+    constexpr int kLine = 16;  // doubles in a 128-byte line
+    const int used = D + 1;
+    const int ntiles = (used + kLine - 1) / kLine;
+    if (wave == 0) {
+        double* row = item + (int64_t)g * width;
+        for (int col = l; col < ntiles * kLine; col += 64) {
+            const int src = col < D ? col : (col == D ? loss_slot : -1);
+            double s = 0.0;
+            if (src >= 0) {
+#pragma unroll
+                for (int w = 0; w < NW; ++w) s += part[w * width + src];
+            }
+            store_agent(row + col, s);
+        }
+    }
+    // Group g owns the tiles g, g + G, ... (tile j: used columns 16 j ..
+    // 16 j + 15).  Its thread t takes column i = t mod 16 of the tile in rows
+    // t / 16, t / 16 + RS, ... (RS = threads / 16), so that each load and
+    // store of a wave covers whole lines, and waits for those slots; the
+    // group adds the G rows of each column in a fixed order (each thread its
+    // rows in order, then the four lanes of a wave that share the column,
+    // then the waves in order) and writes the outputs, and only then marks
+    // the slots empty again for the next call.
+    constexpr int NT = NW * kWave;
+    constexpr int RS = NT / kLine;
+    constexpr int kMaxRows = (kMaxPotentialGroups + RS - 1) / RS;
+    const int mine = g < ntiles ? (ntiles - 1 - g) / G + 1 : 0;
+    if (mine == 0) return;  // uniform over the group
+    const int t = threadIdx.x;
+    const int ic = t & (kLine - 1);
+    const int r0 = t / kLine;
+    const double inv_s2 = 1.0 / (prior_scale * prior_scale);
+    __syncthreads();  // the waves' rows are consumed: LDS is reused below
+    for (int jt = 0; jt < mine; ++jt) {
+        const int c0 = (g + jt * G) * kLine;
+        const int col = c0 + ic;
+        // what the outputs add besides the sums, read before the wait
+        double extra = 0.0;
+        if (col < D) extra = Wk[col] * inv_s2;
+        if (wave == 0 && c0 <= D && D < c0 + kLine) {
+            double pr = 0.0;
+            for (int j = l; j < D; j += kWave) pr += 0.5 * Wk[j] * Wk[j] * inv_s2;
+            const double prior = wave_sum(pr) + (double)D * (log(prior_scale) + kHalfLog2Pi);
+            if (col == D) extra = prior;
+        }
+        // (one poll of the thread's slots at a time: more polls in flight, a
+        // fraction of a round trip apart, made the slots arrive later)
+        unsigned long long v[kMaxRows];
+#pragma unroll
+        for (int m = 0; m < kMaxRows; ++m) {
+            const int r = r0 + m * RS;
+            v[m] = r < G ? load_bits(item + (int64_t)r * width + col) : 0ull;  // 0: +0.0
+        }
+        const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+        for (;;) {
+            bool pending = false;
+#pragma unroll
+            for (int m = 0; m < kMaxRows; ++m) {
+                const int r = r0 + m * RS;
+                if (r < G && v[m] == kEmptyPartial) {
+                    v[m] = load_bits(item + (int64_t)r * width + col);
+                    pending = true;
+                }
+            }
+            if (!pending) break;
+            if (__builtin_amdgcn_s_memrealtime() - t0 > kGatherWaitTicks) {
+                // another call overlapped this one: the results are NaN
+                __hip_atomic_store(failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+                for (int m = 0; m < kMaxRows; ++m) v[m] = v[m] == kEmptyPartial ? 0ull : v[m];
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        double s = 0.0;
+#pragma unroll
+        for (int m = 0; m < kMaxRows; ++m) s += __builtin_bit_cast(double, v[m]);
+        s += xor_move<16>(s);
+        s += xor_move<32>(s);
+        if (l < kLine) part[wave * kLine + l] = s;
+        __syncthreads();  // the waves' sums (and any failure) in LDS
+        if (t < kLine && col <= D) {
+            double tot = 0.0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) tot += part[w * kLine + t];
+            const double bad = *failed ? __builtin_nan("") : 0.0;
+            if (col < D) out_grad[col] = tot + extra + bad;
+            else *out_U = tot + extra + bad;
+        }
+#pragma unroll
+        for (int m = 0; m < kMaxRows; ++m) {
+            const int r = r0 + m * RS;
+            if (r < G) empty_slot(item + (int64_t)r * width + col);  // for the next call
+        }
+        __syncthreads();  // part[] is reused by the next tile
+    }
+}
+
 // The 8-wave shapes run two waves per SIMD (one group per CU), so the
 // compiler may give a lane up to 256 registers: left to aim at four waves
 // per SIMD it squeezed the fp32 stream into 120 and the pass ran slower.
@@ -123,110 +240,160 @@ __global__ void __launch_bounds__((pot_waves<T, S, CPS>() * kWave))
     } else {
         finish_pass_to_row<CPS, S>(acc, loss, row, D, loss_slot);
     }
-    if (threadIdx.x == 0) failed = 0;
-    __syncthreads();  // per-wave sums in LDS
-    // Row g of the item's slots (at item + g * width) holds the group's
-    // partial of each used column: columns 0..D-1, the loss at D, then zeros
-    // up to a whole number of 128-byte lines, so that every store and every
-    // read between groups moves whole lines (a partial-line write to HBM is
-    // a read-modify-write, and those slowed the other groups' streams).
-    constexpr int kLine = 16;  // doubles in a 128-byte line
-    const int used = D + 1;
-    const int ntiles = (used + kLine - 1) / kLine;
-    double* item = partials + k * G * width;
-    if (wave == 0) {
-        double* row = item + (int64_t)g * width;
-        for (int col = l; col < ntiles * kLine; col += 64) {
-            const int src = col < D ? col : (col == D ? loss_slot : -1);
-            double s = 0.0;
-            if (src >= 0) {
+    sum_groups<NW>(part, &failed, W + k * D, D, G, g, width, partials + k * G * width, prior_scale, out_U + k,
+                   out_grad + k * D);
+}
+
+// One position on data in the caller's own row-major layout, read once
+// (nuts_potential_grad: laying the data out first reads it, writes it and
+// reads it again).  A block of R rows is R * D consecutive elements, so a wave
+// loads its blocks as one contiguous run each (64 lanes side by side), turns
+// them round in an LDS region of its own and computes them as
+// potential_grad_kernel does.  The next block's loads are in flight while the current one is
+// computed.  Bound: HBM (one read of X and y).  581,012 x 55 fp64 on the
+// device: 68 us a call (3.8 TB/s with the call's 20 us of launch and wait)
+// from 640 us, of which the layout kernel was 293, and 7 to 12 ms where the
+// device allocations of the layout came around fast enough to wait for freed
+// memory to be cleared.
+template <typename T, int S, int CPS>
+struct RowsBlock {
+    static constexpr int RPL = BlockShape<T, S>::RPL;
+    static constexpr int R = BlockShape<T, S>::R;
+    // the caller's rows are aligned to their elements only
+    typedef T V __attribute__((ext_vector_type(RPL), aligned(sizeof(T))));
+    V raw[CPS];
+    uint8_t y[RPL];
+
+    // Elements (j * 64 + lane) * RPL + i of block b, j < D / S; zeros past row
+    // N.  true if a label of the lane's rows is neither 0 nor 1.
+    __device__ __forceinline__ bool load(const T* __restrict__ X, const uint8_t* __restrict__ yv, int64_t b, int64_t N,
+                                         int D)
+    {
+        const int L = lane();
+        const int64_t row_b = b * R;
+        const T* base = X + row_b * D;
+        const int row0 = (L / S) * RPL;
+        bool bad = false;
+        if (row_b + R <= N) {  // uniform: a whole block
+            const int slots = 64 * D / S;
 #pragma unroll
-                for (int w = 0; w < NW; ++w) s += part[w * width + src];
+            for (int j = 0; j < CPS; ++j) {
+                const int e = j * 64 + L;
+                V v = {};
+                if (e < slots) v = *reinterpret_cast<const V*>(base + (int64_t)e * RPL);
+                raw[j] = v;
             }
-            store_agent(row + col, s);
-        }
-    }
-    // Group g owns the tiles g, g + G, ... (tile j: used columns 16 j ..
-    // 16 j + 15).  Its thread t takes column i = t mod 16 of the tile in rows
-    // t / 16, t / 16 + RS, ... (RS = threads / 16), so that each load and
-    // store of a wave covers whole lines, and waits for those slots; the
-    // group adds the G rows of each column in a fixed order (each thread its
-    // rows in order, then the four lanes of a wave that share the column,
-    // then the waves in order) and writes the outputs, and only then marks
-    // the slots empty again for the next call.
-    constexpr int NT = NW * kWave;
-    constexpr int RS = NT / kLine;
-    constexpr int kMaxRows = (kMaxPotentialGroups + RS - 1) / RS;
-    const int mine = g < ntiles ? (ntiles - 1 - g) / G + 1 : 0;
-    if (mine == 0) return;  // uniform over the group
-    const int t = threadIdx.x;
-    const int ic = t & (kLine - 1);
-    const int r0 = t / kLine;
-    const double inv_s2 = 1.0 / (prior_scale * prior_scale);
-    __syncthreads();  // the waves' rows are consumed: LDS is reused below
-    for (int jt = 0; jt < mine; ++jt) {
-        const int c0 = (g + jt * G) * kLine;
-        const int col = c0 + ic;
-        // what the outputs add besides the sums, read before the wait
-        double extra = 0.0;
-        if (col < D) extra = W[k * D + col] * inv_s2;
-        if (wave == 0 && c0 <= D && D < c0 + kLine) {
-            double pr = 0.0;
-            for (int j = l; j < D; j += kWave) pr += 0.5 * W[k * D + j] * W[k * D + j] * inv_s2;
-            const double prior = wave_sum(pr) + (double)D * (log(prior_scale) + kHalfLog2Pi);
-            if (col == D) extra = prior;
-        }
-        // (one poll of the thread's slots at a time: more polls in flight, a
-        // fraction of a round trip apart, made the slots arrive later)
-        unsigned long long v[kMaxRows];
 #pragma unroll
-        for (int m = 0; m < kMaxRows; ++m) {
-            const int r = r0 + m * RS;
-            v[m] = r < G ? load_bits(item + (int64_t)r * width + col) : 0ull;  // 0: +0.0
-        }
-        const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-        for (;;) {
-            bool pending = false;
+            for (int i = 0; i < RPL; ++i) y[i] = yv[row_b + row0 + i];
+        } else {
+            const int64_t have = (N - row_b) * D;
 #pragma unroll
-            for (int m = 0; m < kMaxRows; ++m) {
-                const int r = r0 + m * RS;
-                if (r < G && v[m] == kEmptyPartial) {
-                    v[m] = load_bits(item + (int64_t)r * width + col);
-                    pending = true;
+            for (int j = 0; j < CPS; ++j) {
+#pragma unroll
+                for (int i = 0; i < RPL; ++i) {
+                    const int e = (j * 64 + L) * RPL + i;
+                    T v = T(0);
+                    if (e < have) v = base[e];
+                    raw[j][i] = v;
                 }
             }
-            if (!pending) break;
-            if (__builtin_amdgcn_s_memrealtime() - t0 > kGatherWaitTicks) {
-                // another call overlapped this one: the results are NaN
-                __hip_atomic_store(&failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 #pragma unroll
-                for (int m = 0; m < kMaxRows; ++m) v[m] = v[m] == kEmptyPartial ? 0ull : v[m];
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-        }
-        double s = 0.0;
-#pragma unroll
-        for (int m = 0; m < kMaxRows; ++m) s += __builtin_bit_cast(double, v[m]);
-        s += xor_move<16>(s);
-        s += xor_move<32>(s);
-        if (l < kLine) part[wave * kLine + l] = s;
-        __syncthreads();  // the waves' sums (and any failure) in LDS
-        if (t < kLine && col <= D) {
-            double tot = 0.0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) tot += part[w * kLine + t];
-            const double bad = failed ? __builtin_nan("") : 0.0;
-            if (col < D) out_grad[k * D + col] = tot + extra + bad;
-            else out_U[k] = tot + extra + bad;
+            for (int i = 0; i < RPL; ++i) y[i] = row_b + row0 + i < N ? yv[row_b + row0 + i] : (uint8_t)0;
         }
 #pragma unroll
-        for (int m = 0; m < kMaxRows; ++m) {
-            const int r = r0 + m * RS;
-            if (r < G) empty_slot(item + (int64_t)r * width + col);  // for the next call
-        }
-        __syncthreads();  // part[] is reused by the next tile
+        for (int i = 0; i < RPL; ++i) bad = bad || y[i] > 1;
+        return bad;
     }
+
+    // Through the wave's LDS region st (R * D elements) into the column slots
+    // of compute_block.
+    __device__ __forceinline__ BlockRegs<T, CPS, S> turn(T* st, int D) const
+    {
+        const int L = lane();
+        const int slots = 64 * D / S;
+#pragma unroll
+        for (int j = 0; j < CPS; ++j) {
+            const int e = j * 64 + L;
+            if (e < slots) {
+#pragma unroll
+                for (int i = 0; i < RPL; ++i) st[e * RPL + i] = raw[j][i];
+            }
+        }
+        // a wave's LDS instructions execute in order; keep the compiler's too
+        __builtin_amdgcn_wave_barrier();
+        asm volatile("" ::: "memory");
+        const int p = L & (S - 1);
+        const T* r0 = st + (L / S) * RPL * D;
+        BlockRegs<T, CPS, S> out;
+#pragma unroll
+        for (int k = 0; k < CPS; ++k) {
+            const int c = k * S + p;
+            T v[RPL];
+#pragma unroll
+            for (int i = 0; i < RPL; ++i) v[i] = c < D ? r0[i * D + (c < D ? c : 0)] : T(0);
+            if constexpr (RPL == 2) {
+                out.x[k].x = v[0];
+                out.x[k].y = v[1];
+            } else {
+                out.x[k] = v[0];
+            }
+        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+        uint32_t yy = y[0];
+        if constexpr (RPL == 2) yy |= (uint32_t)y[1] << 8;
+        out.y = (typename BlockRegs<T, CPS, S>::Y)yy;
+        return out;
+    }
+};
+
+constexpr int kRowsWaves = 8;  // two a SIMD: 256 registers
+
+template <typename T, int S, int CPS>
+__global__ void __launch_bounds__((kRowsWaves * kWave)) __attribute__((amdgpu_waves_per_eu(1, 2))) potential_rows_kernel(
+    PositionArg wa, const T* __restrict__ X, const uint8_t* __restrict__ y, int64_t N, int64_t nb, int D, int G,
+    int width, double* __restrict__ partials, double prior_scale, double* __restrict__ out_U,
+    double* __restrict__ out_grad, unsigned int* __restrict__ bad_label)
+{
+    constexpr int R = BlockShape<T, S>::R;
+    constexpr int NW = kRowsWaves;
+    extern __shared__ double part[];  // [NW][width], then the waves' turning regions
+    __shared__ int failed;
+    const int l = lane();
+    const int wave = threadIdx.x / kWave;
+    const int g = blockIdx.x;
+    const int loss_slot = width - 64;
+    const double* W = wa.device ? wa.device : wa.host;
+    T* st = reinterpret_cast<T*>(part + NW * width) + wave * R * D;
+
+    const int64_t first = (int64_t)g * NW + wave;
+    const int64_t stride = (int64_t)G * NW;
+    RowsBlock<T, S, CPS> a;
+    bool bad = false;
+    if (first < nb) bad = a.load(X, y, first, N, D);
+    double qv[CPS];
+    spread_position_lds<CPS, S>(W, D, qv);
+    double acc[CPS];
+#pragma unroll
+    for (int c = 0; c < CPS; ++c) acc[c] = 0.0;
+    double loss = 0.0;
+#pragma unroll 1
+    for (int64_t b = first; b < nb; b += stride) {
+        const BlockRegs<T, CPS, S> blk = a.turn(st, D);
+        if (b + stride < nb) bad = a.load(X, y, b + stride, N, D) || bad;
+        compute_block<T, CPS, S>(blk, N - b * R, qv, acc, loss);
+    }
+    if (__any(bad) && l == 0) *bad_label = 1u;  // every writer stores the same value
+
+    double* row = part + wave * width;
+    if constexpr (S <= 8) {
+        const double col = finish_pass<CPS, S>(acc, loss);
+        if (l < D) row[l] = col;
+        if (l == 0) row[loss_slot] = loss;
+    } else {
+        finish_pass_to_row<CPS, S>(acc, loss, row, D, loss_slot);
+    }
+    sum_groups<NW>(part, &failed, W, D, G, g, width, partials, prior_scale, out_U, out_grad);
 }
 
 // Many items (K >= kItemMinK) of at most kItemMaxBlocks row blocks and
@@ -312,6 +479,40 @@ hipError_t enqueue(const DataView& dv, double prior_scale, const double* W, int6
     hipLaunchKernelGGL((potential_grad_kernel<T, S, CPS>), dim3(G, (unsigned)K), dim3(NW * kWave), lds, stream, dv,
                        W, G, width, partials, prior_scale, out_U, out_grad);
     return hipGetLastError();
+}
+
+template <typename T, int S, int CPS>
+hipError_t enqueue_rows(const PositionArg& wa, const void* X, const uint8_t* y, int64_t N, int64_t nb, int D, int G,
+                        int width, double prior_scale, double* partials, double* out_U, double* out_grad,
+                        unsigned int* bad_label, hipStream_t stream)
+{
+    constexpr int NW = kRowsWaves;
+    size_t lds = (size_t)NW * (width * sizeof(double) + (size_t)BlockShape<T, S>::R * D * sizeof(T));
+    if (lds < kOwnCuLds) lds = kOwnCuLds;
+    const void* k = (const void*)potential_rows_kernel<T, S, CPS>;
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((potential_rows_kernel<T, S, CPS>), dim3(G), dim3(NW * kWave), lds, stream, wa, (const T*)X, y, N,
+                       nb, D, G, width, partials, prior_scale, out_U, out_grad, bad_label);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t enqueue_rows_shape(const PositionArg& wa, const void* X, const uint8_t* y, int64_t N, int64_t nb, int D,
+                              int G, int width, double prior_scale, double* partials, double* out_U,
+                              double* out_grad, unsigned int* bad_label, hipStream_t stream)
+{
+#define NUTS_ROWS(S_, C_)                                                                                            \
+    return enqueue_rows<T, S_, C_>(wa, X, y, N, nb, D, G, width, prior_scale, partials, out_U, out_grad, bad_label, \
+                                   stream)
+    if (D <= 8) NUTS_ROWS(1, 8);
+    if (D <= 16) NUTS_ROWS(1, 16);
+    if (D <= 32) NUTS_ROWS(4, 8);
+    if (D <= 64) NUTS_ROWS(8, 8);
+    if (D <= 128) NUTS_ROWS(16, 8);
+    if (D <= 256) NUTS_ROWS(32, 8);
+    NUTS_ROWS(32, 10);
+#undef NUTS_ROWS
 }
 
 template <typename T>
@@ -442,6 +643,17 @@ hipError_t launch_potential_grad(const DataView& dv, double prior_scale, const d
                                      out_grad, stream);
     return enqueue_shape<float>(dv, prior_scale, W, K, plan.groups_per_item, plan.width, plan.own_cu, partials, out_U, out_grad,
                                 stream);
+}
+
+hipError_t launch_potential_rows(const PositionArg& wa, const void* X, const uint8_t* y, const DataView& shape,
+                                 double prior_scale, const PotentialPlan& plan, double* partials, double* out_U,
+                                 double* out_grad, unsigned int* bad_label, hipStream_t stream)
+{
+    if (shape.dtype == NUTS_F64)
+        return enqueue_rows_shape<double>(wa, X, y, shape.N, shape.nb, shape.D, plan.groups_per_item, plan.width,
+                                          prior_scale, partials, out_U, out_grad, bad_label, stream);
+    return enqueue_rows_shape<float>(wa, X, y, shape.N, shape.nb, shape.D, plan.groups_per_item, plan.width,
+                                     prior_scale, partials, out_U, out_grad, bad_label, stream);
 }
 
 }  // namespace nuts
