@@ -24,8 +24,10 @@ struct nuts_data {
     uint8_t* y = nullptr;
     // row-stage copy for the batched (matrix-core) path, built on first use
     BatchView batch{};
-    float* bX = nullptr;
-    uint8_t* by = nullptr;
+    void* bX = nullptr;
+    // its fp32 form for the sampler kernels with the optional features
+    float* bX32 = nullptr;
+    uint8_t* by32 = nullptr;
 };
 
 static void free_data_buffers(nuts_data* d)
@@ -33,7 +35,8 @@ static void free_data_buffers(nuts_data* d)
     if (d->X) (void)hipFree(d->X);
     if (d->y) (void)hipFree(d->y);
     if (d->bX) (void)hipFree(d->bX);
-    if (d->by) (void)hipFree(d->by);
+    if (d->bX32) (void)hipFree(d->bX32);
+    if (d->by32) (void)hipFree(d->by32);
 }
 
 struct nuts_handle {
@@ -673,34 +676,54 @@ static int ensure_batch_layout(nuts_handle* h, const nuts_data* dc)
     if (!batch_shape(d->view.D, &kt, &tc))
         return fail(h, NUTS_EUNSUPPORTED, "the batched path takes D <= %d (got %d)", 16 * kBatchMaxKT + 4,
                     d->view.D);
-    BatchView b;
+    BatchView b{};
     b.N = d->view.N;
     b.D = d->view.D;
     b.kt = kt;
     b.tc = tc;
-    b.stride = 16 * batch_kp(kt) + 4;
     b.ns = (b.N + kBatchStageRows - 1) / kBatchStageRows;
-    const size_t xb = (size_t)b.ns * kBatchStageRows * b.stride * sizeof(float);
-    const size_t yb = (size_t)b.ns * kBatchStageRows;
-    float* X = nullptr;
-    uint8_t* y = nullptr;
+    const size_t xb = (size_t)b.ns * batch_stage_bytes(kt);
+    void* X = nullptr;
     if (xb) {
         hipError_t e = hipMalloc(&X, xb);
-        if (e == hipSuccess) e = hipMalloc(&y, yb);
-        if (e == hipSuccess) e = launch_to_batch_layout(d->view, b, X, y, h->stream);
+        if (e == hipSuccess) e = launch_to_batch_layout(d->view, b, X, h->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
         if (e != hipSuccess) {
             if (X) (void)hipFree(X);
-            if (y) (void)hipFree(y);
             return fail(h, e == hipErrorOutOfMemory ? NUTS_ENOMEM : NUTS_EDEVICE, "batched layout: %s",
                         hipGetErrorString(e));
         }
     }
     b.X = X;
-    b.y = y;
     d->batch = b;
     d->bX = X;
-    d->by = y;
+    return NUTS_OK;
+}
+
+// The fp32 layout of a data set that has the row-stage layout (built on first
+// use).
+static int ensure_batch_layout_f32(nuts_handle* h, const nuts_data* dc)
+{
+    nuts_data* d = const_cast<nuts_data*>(dc);
+    if (d->bX32) return NUTS_OK;
+    BatchView& b = d->batch;
+    b.stride32 = batch_stride32(b.kt);
+    const size_t rows = (size_t)b.ns * kBatchStageRows;
+    float* X = nullptr;
+    uint8_t* y = nullptr;
+    hipError_t e = hipMalloc(&X, rows * b.stride32 * sizeof(float));
+    if (e == hipSuccess) e = hipMalloc(&y, rows);
+    if (e == hipSuccess) e = launch_to_batch_layout_f32(d->view, b, X, y, h->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) {
+        if (X) (void)hipFree(X);
+        if (y) (void)hipFree(y);
+        return fail(h, e == hipErrorOutOfMemory ? NUTS_ENOMEM : NUTS_EDEVICE, "batched layout: %s", hipGetErrorString(e));
+    }
+    b.X32 = X;
+    b.y32 = y;
+    d->bX32 = X;
+    d->by32 = y;
     return NUTS_OK;
 }
 
@@ -970,6 +993,10 @@ int nuts_sample_data(nuts_handle* h, const nuts_data* d, uint32_t flags, double 
         HIP_TRY(h, launch_sampler_wave(a, s));
         if (kev) HIP_TRY(h, hipEventRecord(kev[1], s));
     } else if (path == NUTS_PATH_BATCH) {
+        if (sampler_extended(a)) {
+            rc = ensure_batch_layout_f32(h, d);
+            if (rc != NUTS_OK) return rc;
+        }
         // launches of up to kBatchMaxTiles tiles of 128 chains, the groups of
         // the device split evenly between the tiles of a launch
         const int max_tiles = std::min(kBatchMaxTiles, h->num_cu / kBatchTileChains);

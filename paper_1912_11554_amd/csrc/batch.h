@@ -2,26 +2,43 @@
 //
 // One workgroup owns a range of 64-row stages and a tile of 128 positions
 // (chains).  Eight waves each take 16 positions; the stage rows are staged in
-// LDS once and read by all eight.  Per 16-row tile a wave computes
-//   E[16 rows x 16 positions] = X_tile . Q          (v_mfma_f32_16x16x4f32,
-//                                                     contraction over columns)
+// LDS once and read by all eight.  Per pair of 16-row tiles a wave computes
+//   E[16 rows x 16 positions] = X_tile . Q          (contraction over columns)
 //   loss and residual of every (row, position) on E
 //   G[D x 16] += X_tile^T . R                       (contraction over rows)
 // with G held in registers across the whole row range.
 //
-// Operand layout of v_mfma_f32_16x16x4f32 (one 16x16 block): lane l gives
-// A[l % 16][l / 16] and B[l / 16][l % 16]; result register r of lane l is
-// C[4 (l / 16) + r][l % 16].  The contraction index of instruction (chunk t,
-// sub-step i) is column 16 t + 4 (l / 16) + i, so that each lane reads four
-// consecutive columns of its row with one 16-byte LDS load.  For G the
-// contraction index of sub-step r is row 4 (l / 16) + r: exactly the rows whose
-// residuals the lane already holds in register r of the E result, so R feeds
-// the second product without any data movement.
+// The products are fp32 products on the bf16 matrix cores (16 times the rate
+// of the fp32 ones).  Every fp32 factor is split into three bf16 parts, x = x1
+// + x2 + x3 with x1 = bf16(x), x2 = bf16(x - x1), x3 = bf16(x - x1 - x2): 8
+// bits each, so the three hold all 24 bits of x and the split is exact (short
+// of the subnormal range).  x q is then the sum of nine products of bf16
+// parts, each exact in fp32; the six of x1 q1, x1 q2, x2 q1, x1 q3, x2 q2 and
+// x3 q1 are taken, and the three left out are below 2^-25 |x q| together,
+// under half the rounding of one fp32 multiply-add.  The sums are the matrix
+// cores' fp32 accumulations over 32 products at a time (the fp32 instruction
+// rounded after every four).  Against 64-bit arithmetic the gradient of 256
+// positions on 200,000 x 129 is off by 7.4e-7 (8.5e-7 with the fp32
+// instruction), the log-likelihood of 500 draws over 581,012 x 55 by 2.1e-9
+// (2.2e-9).  256 positions on 200,000 x 129 take 167 us a call, from 264; the
+// loop waits for LDS (six reads of every element per wave and pass, about as
+// many cycles as the products) and the matrix cores in turn: reading the next
+// step's operands ahead of the current products changed nothing (166.5 us).
 //
-// Precision: X and Q are fp32 and products accumulate in fp32 inside the
-// matrix cores; the row terms use the fp32 hardware exp/log/rcp; the loss is
-// accumulated in fp64 per lane and all partial rows are added in fp64 in a
-// fixed order.
+// v_mfma_f32_16x16x32_bf16: lane l gives A[l % 16][8 (l / 16) + i] and
+// B[8 (l / 16) + i][l % 16], i < 8; result register r of lane l is
+// C[4 (l / 16) + r][l % 16].  For E the contraction index 8 (l / 16) + i of
+// K-step t is column 32 t + 8 (l / 16) + i: one 16-byte LDS read a part.  For G
+// the contraction index 8 (l / 16) + i is row 4 (l / 16) + i of the pair's
+// first tile (i < 4) or row 4 (l / 16) + i - 4 of its second: exactly the rows
+// whose residuals the lane already holds from the E results, so R feeds the
+// second product without any data movement; its X operand, a column's four
+// rows, comes from the row-major stage by transposing LDS reads
+// (ds_read_b64_tr_b16: lane i of 16 receives element i of each of the four
+// rows the 16 lanes read).
+//
+// The row terms use the fp32 hardware exp/log/rcp; the loss is accumulated in
+// fp64 per lane and all partial rows are added in fp64 in a fixed order.
 #pragma once
 
 #include "device.h"
@@ -31,47 +48,67 @@ namespace nuts {
 namespace batch {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef short v4s __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 8;                                   // matrix-core waves per group
 constexpr int kTileRows = 16;
 constexpr int kTiles = kBatchStageRows / kTileRows;         // MFMA tiles per stage
 constexpr int kTail = 4;
-constexpr int kMaxStride = 16 * kBatchMaxKT + kTail;        // 132 floats per row in HBM
+constexpr int kParts = 3;                                   // bf16 parts of a factor
 
-// LDS geometry of a stage for KT chunks.  The HBM row (16 KP permuted
-// matrix-core slots, then the tail) is spread out so that column residue g
-// starts at g * GS: GS = 12 for KP = 8 (two 16-byte pieces per residue) and
-// 4 for KP = 4, and the row stride RS = 16 GS + 4 is 4 mod 64 floats.  With
-// these, a 16-lane phase of every 16-byte LDS read below (16 rows at one
-// residue, or 16 residues of one row) touches 64 distinct banks.
+// Geometry of a stage image (the same in memory and in LDS): three planes (the
+// bf16 parts) of 64 rows of kCols columns, then the tail columns (fp32, four a
+// row), then the labels as signs 1 - 2 y (fp32).  A row is kSlots 16-byte
+// slots; slot s of row r sits at position s ^ swizzle(r).  With it every phase
+// of the LDS reads touches all 64 banks once: a phase of the column
+// contraction's 16-byte reads takes lanes 0..3, 12..15 and 20..27 (or the other
+// 16 of a half wave), that is all 16 rows, rows 4..11 at the neighbour of the
+// others' slot; a phase of the row contraction's 8-byte reads takes 32 lanes,
+// 8 rows with two neighbouring slots each.
 template <int KT>
 struct Geo {
-    static constexpr int KP = (KT + 3) / 4 * 4;
-    static constexpr int GS = KP == 8 ? 12 : 4;
-    static constexpr int RS = 16 * GS + 4;
-    static constexpr int HS = 16 * KP + 4;          // HBM row: floats
-    static constexpr int HV = HS / 4;               // HBM row: 16-byte pieces
+    static constexpr int kCols = batch_cols(KT);
+    static constexpr int kSteps = (KT + 1) / 2;              // K-steps of 32 columns
+    static constexpr int kSlots = kCols / 8;
+    static constexpr int kRow = kCols * 2;                   // bytes
+    static constexpr int kPlane = kBatchStageRows * kRow;
+    static constexpr int kTailAt = kParts * kPlane;
+    static constexpr int kSignAt = kTailAt + kBatchStageRows * kTail * 4;
+    static constexpr int kBytes = kSignAt + kBatchStageRows * 4;
+    static_assert(kBytes == batch_stage_bytes(KT), "the host sizes stages as the kernels read them");
 };
-constexpr int kStageFloats = kBatchStageRows * Geo<kBatchMaxKT>::RS;  // largest LDS stage
-constexpr int kStageBuf = kStageFloats + 4;                          // plus one junk 16-byte slot
-constexpr int kStageVecs = (kBatchStageRows * kMaxStride / 4 + kWaves * kWave - 1) / (kWaves * kWave);
 
-// Column of the matrix-core operand that lane group jj reads as component i
-// of its 16-byte piece in chunk t of the column contraction (E = X Q):
-// piece f = 4 t + jj of the row is residue g, half h of the permuted slots.
-template <int KT>
-__host__ __device__ constexpr int e_column(int t, int jj, int i)
+// bf16 parts of n fp32 values, part by part.
+__device__ __forceinline__ void split3(v2f x, v2bf& a, v2bf& b, v2bf& c)
 {
-    constexpr int KP = Geo<KT>::KP;
-    const int f = 4 * t + jj;
-    const int g = KP == 8 ? f >> 1 : f;
-    const int h = KP == 8 ? f & 1 : 0;
-    return 16 * (4 * h + i) + g;   // chunk 4 h + i (valid if < KT), residue g
+    a = __builtin_convertvector(x, v2bf);
+    x -= __builtin_convertvector(a, v2f);  // exact
+    b = __builtin_convertvector(x, v2bf);
+    x -= __builtin_convertvector(b, v2f);  // exact
+    c = __builtin_convertvector(x, v2bf);  // exact
+}
+__device__ __forceinline__ void split3(const float (&x)[8], v8bf (&out)[kParts])
+{
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+        v2bf a, b, c;
+        split3(v2f{x[i], x[i + 1]}, a, b, c);
+        out[0][i] = a[0];
+        out[0][i + 1] = a[1];
+        out[1][i] = b[0];
+        out[1][i + 1] = b[1];
+        out[2][i] = c[0];
+        out[2][i + 1] = c[1];
+    }
 }
 
-__device__ __forceinline__ v4f mfma(float a, float b, v4f c)
+__device__ __forceinline__ v4f mfma(v8bf a, v8bf b, v4f c)
 {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
 // Negative log-likelihood and residual of one (row, position) from eta in
@@ -79,9 +116,11 @@ __device__ __forceinline__ v4f mfma(float a, float b, v4f c)
 // ln 2 log2(1 + e), residual = sgn sigmoid(t), e = exp(-|t|); three
 // transcendentals (exp2, log2, reciprocal) on the fp32 hardware units.  The
 // rounding of 1 + e costs at most 2^-24 absolute per term (log1p accuracy is
-// not needed for a sum of softplus values that are O(1) each).  Padding rows
-// (zero X, y = 0) have eta = 0 exactly and add exactly ln 2 (in fp32) to the
-// loss and nothing to the gradient; the caller subtracts them.
+// not needed for a sum of softplus values that are O(1) each; one logarithm
+// for the product of four rows' 1 + e was 5 times as far off over 581,012
+// rows).  Padding rows (zero X, y = 0) have eta = 0 exactly and add exactly
+// ln 2 (in fp32) to the loss and nothing to the gradient; the caller subtracts
+// them.
 constexpr float kLn2f = 0.69314718055994531f;
 
 __device__ __forceinline__ void row_terms(float eta, float sgn, float& loss, float& resid)
@@ -94,11 +133,11 @@ __device__ __forceinline__ void row_terms(float eta, float sgn, float& loss, flo
     resid = sgn * ((t >= 0.0f ? 1.0f : e) * inv);
 }
 
-// A wave's share of the positions: Q in the B-operand order of the column
-// contraction (q[4 t + i] = Q[e_column(t, l / 16, i)][l % 16], zero where
-// that chunk is >= KT) and the tail.
+// A wave's share of the positions: the bf16 parts of Q in the B-operand order
+// of the column contraction (q[p][t][i] = part p of Q[32 t + 8 (l / 16) +
+// i][l % 16], zero past the matrix columns) and the tail in fp32.
 struct WaveQ {
-    float q[4 * kBatchMaxKT];
+    v8bf q[kParts][kBatchMaxKT / 2];
     float qt[kTail];
 };
 
@@ -117,167 +156,190 @@ __device__ __forceinline__ void zero(WaveAcc& a)
     a.loss = 0.0;
 }
 
-// Registers of one stage on its way from HBM to LDS; thread `tid` of the
-// kWaves * 64 loaders moves 16-byte pieces tid, tid + 512, ...
-struct StageRegs {
-    v4f v[kStageVecs];  // clang vector type: HIP's float4 class would pin the registers to scratch
-    uint32_t y;
-};
-
-// RECOMPUTE (the sampler kernel, whose nine waves leave 168 registers a
-// lane): the piece offsets are recomputed at every stage.  Hoisted out of the
-// stage loop they were kept in scratch memory there, and each reload waited
-// for every load issued before it, so the stage's loads went out one by one.
-// Kernels with registers to spare keep them (recomputing cost them time).
-template <bool RECOMPUTE>
-__device__ __forceinline__ void load_stage(const BatchView& bv, int64_t st, int tid, StageRegs& r)
-{
-    if constexpr (RECOMPUTE) {
-        int opaque_zero;
-        asm volatile("v_mov_b32 %0, 0" : "=v"(opaque_zero));
-        tid += opaque_zero;
-    }
-    const int last = kBatchStageRows * bv.stride / 4 - 1;
-    const v4f* src = reinterpret_cast<const v4f*>(bv.X + st * kBatchStageRows * bv.stride);
-    const uint32_t* ysrc = reinterpret_cast<const uint32_t*>(bv.y + st * kBatchStageRows);
-    // with RECOMPUTE the labels first: whatever their address waits for (a
-    // register reloaded from scratch waits for every load before it) is then
-    // not the stage's pieces
-    if (RECOMPUTE && tid < kBatchStageRows / 4) r.y = ysrc[tid];
-    // unconditional loads (pieces past the stage re-read its last piece and
-    // are not stored), so the loop unrolls into straight-line code
-#pragma unroll
-    for (int i = 0; i < kStageVecs; ++i) r.v[i] = src[min(tid + i * kWaves * kWave, last)];
-    if (!RECOMPUTE && tid < kBatchStageRows / 4) r.y = ysrc[tid];
-}
-
-// Scatter a stage into the LDS geometry: HBM piece q of a row goes to
-// residue q / (KP / 4), half q % (KP / 4); the last piece is the tail.
-// RECOMPUTE as for load_stage: the destinations are recomputed at every
-// stage (a few integer instructions) instead of reloaded from scratch.
-template <int KT, bool RECOMPUTE>
-__device__ __forceinline__ void store_stage(const StageRegs& r, int tid, float* xs, float* ys)
-{
-    using G = Geo<KT>;
-    constexpr int last = kBatchStageRows * G::HV - 1;
-    if constexpr (RECOMPUTE) {
-        int opaque_zero;
-        asm volatile("v_mov_b32 %0, 0" : "=v"(opaque_zero));
-        tid += opaque_zero;
-    }
-#pragma unroll
-    for (int i = 0; i < kStageVecs; ++i) {
-        const int idx = tid + i * kWaves * kWave;
-        const int row = idx / G::HV;
-        const int q = idx - row * G::HV;
-        int dst;
-        if constexpr (G::KP == 8) dst = q < 32 ? (q >> 1) * 3 + (q & 1) : 4 * G::GS;
-        else dst = q < 4 * G::KP ? q : 4 * G::GS;  // KP = 4: one piece per residue
-        dst += row * (G::RS / 4);
-        // pieces past the stage go to a junk slot after the buffer (never read)
-        reinterpret_cast<v4f*>(xs)[idx <= last ? dst : kStageFloats / 4] = r.v[i];
-    }
-    if (tid < kBatchStageRows / 4) {
-        // labels as signs 1 - 2y
-        v4f sg;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) sg[k] = ((r.y >> (8 * k)) & 1u) ? -1.0f : 1.0f;
-        reinterpret_cast<v4f*>(ys)[tid] = sg;
-    }
-}
-
-// All four 16-row tiles of one LDS stage for this wave's 16 positions, two
-// tiles at a time so that two independent accumulation chains alternate on
-// the matrix core.  KT is the chunk count; the four tail slots are always
-// processed (slots past the tail hold zero columns and zero positions, so
-// they add nothing).
-//
-// `flip` reverses the pair order: the two waves that share a SIMD (loader
-// index w and w + 4) take the pairs in opposite orders.  Each wave raises its
-// issue priority while it feeds the matrix core and lowers it for the row
-// terms: left to the default (the older wave first), the younger wave of a
-// SIMD fell a third behind within each stage and the older one waited for it
-// at the stage barrier.
+// Copy stage st into LDS at `buf` straight from memory (no registers in
+// between); thread tid of the kWaves * 64 loaders moves the 16-byte pieces
+// tid, tid + 512, ...  The copies are outstanding memory operations of the
+// wave until wait_stage.  (An instruction of the compiler's own would make it
+// wait for them before every LDS read of the other buffer, which it cannot
+// tell apart.  m0 is set and used inside one asm block; nothing else in these
+// kernels keeps a value in it.  The five wait states before the load are those
+// between a vector instruction that writes a scalar register, which may have
+// just reloaded the address, and a memory instruction that reads it: the
+// compiler does not see the load inside the block and adds none.)
 template <int KT>
-__device__ __forceinline__ void compute_stage(const float* __restrict__ xs, const float* __restrict__ ys,
-                                              const WaveQ& Q, WaveAcc& acc, bool flip, int pair_lo, int pair_hi)
+__device__ __forceinline__ void load_stage(const BatchView& bv, int64_t st, int tid, char* buf)
+{
+    constexpr int kPieces = Geo<KT>::kBytes / 16;
+    constexpr int kThreads = kWaves * kWave;
+    const char* src = reinterpret_cast<const char*>(bv.X) + st * Geo<KT>::kBytes;
+    const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)buf;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane((uint32_t)(tid / kWave)) * (kWave * 16);
+#pragma unroll
+    for (int i = 0; i * kThreads < kPieces; ++i) {
+        // a lane writes its piece 16 bytes past its neighbour's, from the
+        // wave's LDS address in m0
+        if ((i + 1) * kThreads <= kPieces || i * kThreads + tid < kPieces) {
+            const uint32_t at = __builtin_amdgcn_readfirstlane(lds + i * kThreads * 16 + wave);
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2"
+                         :
+                         : "s"(at), "v"((uint32_t)tid * 16), "s"(src + i * kThreads * 16)
+                         : "memory");
+        }
+    }
+}
+
+// Every outstanding memory operation of the wave, its copies among them.
+__device__ __forceinline__ void wait_stage() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Position swizzle of the 16-byte slots of row r of a 16-row tile.
+template <int KT>
+__device__ __forceinline__ int swizzle(int r)
+{
+    constexpr int n = Geo<KT>::kSlots;
+    if constexpr (n < 2) return 0;
+    const int rr = r / (16 / n);  // rows that share the 64 banks
+    const int middle = ((r >> 2) ^ (r >> 3)) & 1;  // rows 4 .. 11
+    return (((rr & (n / 2 - 1)) << 1) | (rr / (n / 2))) ^ middle;
+}
+
+__device__ __forceinline__ v8bf read_rows(const char* p) { return *reinterpret_cast<const v8bf*>(p); }
+
+__device__ __forceinline__ v4bf read_transposed(const char* p)
+{
+    const v4s v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (__attribute__((address_space(3))) v4s*)(__attribute__((address_space(3))) char*)const_cast<char*>(p));
+    return __builtin_bit_cast(v4bf, v);
+}
+
+// E of the stage's tiles tp and tp + 1 for this wave's positions: the leading
+// products and the corrections in accumulators of their own (four independent
+// chains on the matrix core), then the tail columns where the data has any.
+template <int KT>
+__device__ __forceinline__ void columns(const char* xs, const WaveQ& Q, int tp, bool tail, v4f& e0, v4f& e1)
 {
     using G = Geo<KT>;
     const int l = lane();
     const int m = l & 15;
     const int jj = l >> 4;
-    // this lane's piece of chunk 0 in its E row, and its G residue
-    const int e_off = m * G::RS + (G::KP == 8 ? 12 * (jj >> 1) + 4 * (jj & 1) : 4 * jj);
-    constexpr int e_step = G::KP == 8 ? 24 : 16;
-    const int g_off = 4 * jj * G::RS + m * G::GS;
+    e0 = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    e1 = e0;
+    if constexpr (KT > 0) {
+        v4f c0 = e0, c1 = e0;
+        const char* row = xs + (tp * kTileRows + m) * G::kRow;
+        const int at = (jj ^ swizzle<KT>(m)) * 16;
+#pragma unroll
+        for (int t = 0; t < G::kSteps; ++t) {
+            const char* p0 = row + (at ^ (4 * t * 16));
+            const char* p1 = p0 + kTileRows * G::kRow;
+            const v8bf x0 = read_rows(p0), x1 = read_rows(p1);
+            const v8bf y0 = read_rows(p0 + G::kPlane), y1 = read_rows(p1 + G::kPlane);
+            const v8bf z0 = read_rows(p0 + 2 * G::kPlane), z1 = read_rows(p1 + 2 * G::kPlane);
+            e0 = mfma(x0, Q.q[0][t], e0);
+            e1 = mfma(x1, Q.q[0][t], e1);
+            c0 = mfma(x0, Q.q[1][t], c0);
+            c1 = mfma(x1, Q.q[1][t], c1);
+            c0 = mfma(y0, Q.q[0][t], c0);
+            c1 = mfma(y1, Q.q[0][t], c1);
+            c0 = mfma(x0, Q.q[2][t], c0);
+            c1 = mfma(x1, Q.q[2][t], c1);
+            c0 = mfma(y0, Q.q[1][t], c0);
+            c1 = mfma(y1, Q.q[1][t], c1);
+            c0 = mfma(z0, Q.q[0][t], c0);
+            c1 = mfma(z1, Q.q[0][t], c1);
+        }
+        e0 += c0;
+        e1 += c1;
+    }
+    if (tail) {  // uniform
+        const char* x = xs + G::kTailAt + (tp * kTileRows + 4 * jj) * (kTail * 4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const v4f a = *reinterpret_cast<const v4f*>(x + r * kTail * 4);
+            const v4f b = *reinterpret_cast<const v4f*>(x + (kTileRows + r) * kTail * 4);
+            e0[r] += ((a[0] * Q.qt[0] + a[1] * Q.qt[1]) + a[2] * Q.qt[2]) + a[3] * Q.qt[3];
+            e1[r] += ((b[0] * Q.qt[0] + b[1] * Q.qt[1]) + b[2] * Q.qt[2]) + b[3] * Q.qt[3];
+        }
+    }
+}
+
+// All four 16-row tiles of one LDS stage for this wave's 16 positions, in
+// pairs (32 rows: one K-step of the row contraction).
+//
+// `flip` reverses the pair order: the two waves that share a SIMD (loader
+// index w and w + 4) take the pairs in opposite orders.  Each wave raises its
+// issue priority while it feeds the matrix core and lowers it for the row
+// terms, so that one wave of a SIMD feeds the matrix core while the other
+// does its row terms.
+template <int KT>
+__device__ __forceinline__ void compute_stage(const char* xs, const WaveQ& Q, WaveAcc& acc, bool flip, int pair_lo,
+                                              int pair_hi, bool tail)
+{
+    using G = Geo<KT>;
+    const int l = lane();
+    const int jj = l >> 4;
 #pragma unroll 1
     for (int step = 0; step < kTiles; step += 2) {
         const int tp = flip ? kTiles - 2 - step : step;
         if (tp / 2 < pair_lo || tp / 2 >= pair_hi) continue;  // uniform: another group's rows
-        const float* x0 = xs + tp * kTileRows * G::RS;
-        const float* x1 = x0 + kTileRows * G::RS;
-        v4f e0 = {0.0f, 0.0f, 0.0f, 0.0f};
-        v4f e1 = {0.0f, 0.0f, 0.0f, 0.0f};
+        v4f e0, e1;
         __builtin_amdgcn_s_setprio(2);
-#pragma unroll
-        for (int t = 0; t < G::KP; ++t) {
-            const v4f a0 = *reinterpret_cast<const v4f*>(x0 + e_off + e_step * t);
-            const v4f a1 = *reinterpret_cast<const v4f*>(x1 + e_off + e_step * t);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                e0 = mfma(a0[i], Q.q[4 * t + i], e0);
-                e1 = mfma(a1[i], Q.q[4 * t + i], e1);
-            }
-        }
+        columns<KT>(xs, Q, tp, tail, e0, e1);
         __builtin_amdgcn_s_setprio(0);
-        // tail slots of this lane's four rows 4 jj + r of both tiles
-        v4f xr0[4], xr1[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            xr0[r] = *reinterpret_cast<const v4f*>(x0 + (4 * jj + r) * G::RS + 16 * G::GS);
-            xr1[r] = *reinterpret_cast<const v4f*>(x1 + (4 * jj + r) * G::RS + 16 * G::GS);
-            e0[r] += ((xr0[r][0] * Q.qt[0] + xr0[r][1] * Q.qt[1]) + xr0[r][2] * Q.qt[2]) + xr0[r][3] * Q.qt[3];
-            e1[r] += ((xr1[r][0] * Q.qt[0] + xr1[r][1] * Q.qt[1]) + xr1[r][2] * Q.qt[2]) + xr1[r][3] * Q.qt[3];
-        }
-        const v4f s0 = *reinterpret_cast<const v4f*>(ys + tp * kTileRows + 4 * jj);
-        const v4f s1 = *reinterpret_cast<const v4f*>(ys + (tp + 1) * kTileRows + 4 * jj);
-        float r0[4], r1[4];
+        const char* sg = xs + G::kSignAt + (tp * kTileRows + 4 * jj) * 4;
+        const v4f s0 = *reinterpret_cast<const v4f*>(sg);
+        const v4f s1 = *reinterpret_cast<const v4f*>(sg + kTileRows * 4);
+        float res[8];
         float lsum = 0.0f;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             float l0, l1;
-            row_terms(e0[r], s0[r], l0, r0[r]);
-            row_terms(e1[r], s1[r], l1, r1[r]);
+            row_terms(e0[r], s0[r], l0, res[r]);
+            row_terms(e1[r], s1[r], l1, res[4 + r]);
             lsum += l0 + l1;
         }
         acc.loss += (double)lsum;
-        __builtin_amdgcn_s_setprio(2);
-        // G: residue m of row 4 jj + r holds chunks 4 h .. 4 h + 3 in piece h
+        if constexpr (KT > 0) {
+            v8bf R[kParts];
+            split3(res, R);
+            // lane i of a 16-lane group reads columns 4 (i % 4) .. + 3 of row
+            // 4 jj + i / 4 of a 16-column chunk
+            const int i = l & 15;
+            const int row = 4 * jj + (i >> 2);
+            const char* base = xs + (tp * kTileRows + row) * G::kRow + (i & 1) * 8;
+            const int at = (((i & 3) >> 1) ^ swizzle<KT>(row)) * 16;
+            __builtin_amdgcn_s_setprio(2);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+            for (int mt = 0; mt < KT; ++mt) {
+                const char* p = base + (at ^ (2 * mt * 16));
+                v8bf x[kParts];
 #pragma unroll
-            for (int h = 0; h < G::KP / 4; ++h) {
-                const v4f b0 = *reinterpret_cast<const v4f*>(x0 + g_off + r * G::RS + 4 * h);
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (4 * h + i < KT) acc.g[4 * h + i] = mfma(b0[i], r0[r], acc.g[4 * h + i]);
+                for (int q = 0; q < kParts; ++q) {
+                    const v4bf a = read_transposed(p + q * G::kPlane);
+                    const v4bf b = read_transposed(p + q * G::kPlane + kTileRows * G::kRow);
+                    x[q] = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+                }
+                // the corrections in a sum of their own: two roundings of the
+                // running sum per 32 rows instead of six
+                v4f c = {0.0f, 0.0f, 0.0f, 0.0f};
+                c = mfma(x[0], R[1], c);
+                acc.g[mt] = mfma(x[0], R[0], acc.g[mt]);
+                c = mfma(x[1], R[0], c);
+                c = mfma(x[0], R[2], c);
+                c = mfma(x[1], R[1], c);
+                c = mfma(x[2], R[0], c);
+                acc.g[mt] += c;
             }
+            __builtin_amdgcn_s_setprio(0);
         }
+        if (tail) {
+            const char* x = xs + G::kTailAt + (tp * kTileRows + 4 * jj) * (kTail * 4);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < 4; ++r) {
+                const v4f a = *reinterpret_cast<const v4f*>(x + r * kTail * 4);
+                const v4f b = *reinterpret_cast<const v4f*>(x + (kTileRows + r) * kTail * 4);
 #pragma unroll
-            for (int h = 0; h < G::KP / 4; ++h) {
-                const v4f b1 = *reinterpret_cast<const v4f*>(x1 + g_off + r * G::RS + 4 * h);
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (4 * h + i < KT) acc.g[4 * h + i] = mfma(b1[i], r1[r], acc.g[4 * h + i]);
+                for (int k = 0; k < kTail; ++k) acc.gt[k] += a[k] * res[r] + b[k] * res[4 + r];
             }
-        }
-        __builtin_amdgcn_s_setprio(0);
-#pragma unroll
-        for (int k = 0; k < kTail; ++k) {
-            acc.gt[k] += ((xr0[0][k] * r0[0] + xr0[1][k] * r0[1]) + xr0[2][k] * r0[2]) + xr0[3][k] * r0[3];
-            acc.gt[k] += ((xr1[0][k] * r1[0] + xr1[1][k] * r1[1]) + xr1[2][k] * r1[2]) + xr1[3][k] * r1[3];
         }
     }
 }
@@ -349,43 +411,20 @@ __device__ __forceinline__ void predict_rows(const PredictOut& po, int64_t r0, c
 // its live positions for each of the 64 rows into rs[0..63]; with SAMPLE,
 // the position's predictive samples of the stage's rows.
 template <int KT, bool PRED, bool SAMPLE>
-__device__ __forceinline__ void compute_stage_ll(const float* __restrict__ xs, const float* __restrict__ ys,
-                                                 const WaveQ& Q, float live, double& loss, float* rs,
+__device__ __forceinline__ void compute_stage_ll(const char* xs, const WaveQ& Q, float live, double& loss, float* rs,
                                                  const PredictOut& po, bool tail)
 {
     using G = Geo<KT>;
     const int l = lane();
     const int m = l & 15;
     const int jj = l >> 4;
-    const int e_off = m * G::RS + (G::KP == 8 ? 12 * (jj >> 1) + 4 * (jj & 1) : 4 * jj);
-    constexpr int e_step = G::KP == 8 ? 24 : 16;
 #pragma unroll 1
     for (int tp = 0; tp < kTiles; tp += 2) {
-        const float* x0 = xs + tp * kTileRows * G::RS;
-        const float* x1 = x0 + kTileRows * G::RS;
-        v4f e0 = {0.0f, 0.0f, 0.0f, 0.0f};
-        v4f e1 = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int t = 0; t < G::KP; ++t) {
-            const v4f a0 = *reinterpret_cast<const v4f*>(x0 + e_off + e_step * t);
-            const v4f a1 = *reinterpret_cast<const v4f*>(x1 + e_off + e_step * t);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                e0 = mfma(a0[i], Q.q[4 * t + i], e0);
-                e1 = mfma(a1[i], Q.q[4 * t + i], e1);
-            }
-        }
-        if (tail) {  // uniform: the data has tail columns
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const v4f xr0 = *reinterpret_cast<const v4f*>(x0 + (4 * jj + r) * G::RS + 16 * G::GS);
-                const v4f xr1 = *reinterpret_cast<const v4f*>(x1 + (4 * jj + r) * G::RS + 16 * G::GS);
-                e0[r] += ((xr0[0] * Q.qt[0] + xr0[1] * Q.qt[1]) + xr0[2] * Q.qt[2]) + xr0[3] * Q.qt[3];
-                e1[r] += ((xr1[0] * Q.qt[0] + xr1[1] * Q.qt[1]) + xr1[2] * Q.qt[2]) + xr1[3] * Q.qt[3];
-            }
-        }
-        const v4f s0 = *reinterpret_cast<const v4f*>(ys + tp * kTileRows + 4 * jj);
-        const v4f s1 = *reinterpret_cast<const v4f*>(ys + (tp + 1) * kTileRows + 4 * jj);
+        v4f e0, e1;
+        columns<KT>(xs, Q, tp, tail, e0, e1);
+        const char* sg = xs + G::kSignAt + (tp * kTileRows + 4 * jj) * 4;
+        const v4f s0 = *reinterpret_cast<const v4f*>(sg);
+        const v4f s1 = *reinterpret_cast<const v4f*>(sg + kTileRows * 4);
         float lsum = 0.0f;
         float p0[4], p1[4];
 #pragma unroll
@@ -395,7 +434,7 @@ __device__ __forceinline__ void compute_stage_ll(const float* __restrict__ xs, c
             ll_terms(e1[r], s1[r], l1, p1[r]);
             lsum += l0 + l1;
         }
-        loss += (double)lsum;
+        if constexpr (!SAMPLE) loss += (double)lsum;
         if constexpr (SAMPLE) {
             if (po.y) {
                 predict_rows(po, po.row0 + tp * kTileRows + 4 * jj, p0);
@@ -421,9 +460,9 @@ __device__ __forceinline__ void compute_stage_ll(const float* __restrict__ xs, c
 // order and stored to prow[stage * 64 + row] one stage later, after the
 // barrier that ends it.
 template <int KT, bool PRED, bool SAMPLE>
-__device__ __forceinline__ void stage_loop_ll(const BatchView& bv, int64_t st0, int64_t st1, int tid, float* xs,
-                                              float* ys, float* rs, const WaveQ& Q, float live, double& loss,
-                                              float* prow, PredictOut po)
+__device__ __forceinline__ void stage_loop_ll(const BatchView& bv, int64_t st0, int64_t st1, int tid, char* xs,
+                                              float* rs, const WaveQ& Q, float live, double& loss, float* prow,
+                                              PredictOut po)
 {
     const int widx = tid / kWave;
     auto flush = [&](int64_t st, int b) {
@@ -434,22 +473,17 @@ __device__ __forceinline__ void stage_loop_ll(const BatchView& bv, int64_t st0, 
             prow[st * kBatchStageRows + tid] = s_;
         }
     };
-    if (st0 < st1) {
-        StageRegs r;
-        load_stage<false>(bv, st0, tid, r);
-        store_stage<KT, false>(r, tid, xs, ys);
-    }
+    if (st0 < st1) load_stage<KT>(bv, st0, tid, xs);
+    wait_stage();
     __syncthreads();
     for (int64_t st = st0; st < st1; ++st) {
         const int b = (int)((st - st0) & 1);
-        const bool more = st + 1 < st1;
-        StageRegs r;
-        if (more) load_stage<false>(bv, st + 1, tid, r);
+        if (st + 1 < st1) load_stage<KT>(bv, st + 1, tid, xs + (b ^ 1) * Geo<KT>::kBytes);
         if (st > st0) flush(st - 1, b ^ 1);
         po.row0 = st * kBatchStageRows;
-        compute_stage_ll<KT, PRED, SAMPLE>(xs + b * kStageBuf, ys + b * kBatchStageRows, Q, live, loss,
+        compute_stage_ll<KT, PRED, SAMPLE>(xs + b * Geo<KT>::kBytes, Q, live, loss,
                                            rs + (b * kWaves + widx) * kBatchStageRows, po, bv.tc > 0);
-        if (more) store_stage<KT, false>(r, tid, xs + (b ^ 1) * kStageBuf, ys + (b ^ 1) * kBatchStageRows);
+        wait_stage();
         __syncthreads();
     }
     if (st1 > st0) flush(st1 - 1, (int)((st1 - 1 - st0) & 1));
@@ -470,32 +504,26 @@ __host__ __device__ inline void group_halves(int64_t ns, int64_t i, int64_t grou
 // with double-buffered LDS stages.  Workers (tid = loader index, 0 .. 511)
 // load and compute; a non-worker wave of the same group passes the same
 // workgroup barriers (one more than the stages) and does nothing else.
-// RECOMPUTE as for load_stage.
-template <int KT, bool WORKER, bool RECOMPUTE = false>
-__device__ __forceinline__ void stage_loop(const BatchView& bv, int64_t h0, int64_t h1, int tid, float* xs,
-                                           float* ys, const WaveQ& Q, WaveAcc& acc)
+template <int KT, bool WORKER>
+__device__ __forceinline__ void stage_loop(const BatchView& bv, int64_t h0, int64_t h1, int tid, char* xs,
+                                           const WaveQ& Q, WaveAcc& acc)
 {
     const int64_t st0 = h0 / 2;
     const int64_t st1 = h1 > h0 ? (h1 + 1) / 2 : st0;
     if constexpr (!WORKER) {
         for (int64_t st = st0; st <= st1; ++st) __syncthreads();
     } else {
-        if (st0 < st1) {
-            StageRegs r;
-            load_stage<RECOMPUTE>(bv, st0, tid, r);
-            store_stage<KT, RECOMPUTE>(r, tid, xs, ys);
-        }
+        if (st0 < st1) load_stage<KT>(bv, st0, tid, xs);
+        wait_stage();
         __syncthreads();
         for (int64_t st = st0; st < st1; ++st) {
             const int b = (int)((st - st0) & 1);
-            const bool more = st + 1 < st1;
-            StageRegs r;
-            if (more) load_stage<RECOMPUTE>(bv, st + 1, tid, r);
+            if (st + 1 < st1) load_stage<KT>(bv, st + 1, tid, xs + (b ^ 1) * Geo<KT>::kBytes);
             // the halves of this stage that are the group's
             const int lo = (int)(h0 > 2 * st ? h0 - 2 * st : 0);
             const int hi = (int)(h1 < 2 * st + 2 ? h1 - 2 * st : 2);
-            compute_stage<KT>(xs + b * kStageBuf, ys + b * kBatchStageRows, Q, acc, tid >= 4 * kWave, lo, hi);
-            if (more) store_stage<KT, RECOMPUTE>(r, tid, xs + (b ^ 1) * kStageBuf, ys + (b ^ 1) * kBatchStageRows);
+            compute_stage<KT>(xs + b * Geo<KT>::kBytes, Q, acc, tid >= 4 * kWave, lo, hi, bv.tc > 0);
+            wait_stage();
             __syncthreads();
         }
     }

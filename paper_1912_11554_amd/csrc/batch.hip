@@ -3,6 +3,7 @@
 // products over X, and the persistent sampler that drives 128 chains per tile
 // with it, one leapfrog step of every chain per pass.
 #include "batch.h"
+#include "batch_f32.h"
 #include "sampler_impl.h"
 
 namespace nuts {
@@ -10,9 +11,70 @@ namespace nuts {
 // ---------------------------------------------------------------------------
 // Layout conversion: column blocks (fp32, one data set) -> 64-row stages.
 
+// One thread per row and 16-byte slot of a stage (8 columns, all three parts),
+// or its tail and sign; consecutive threads take consecutive rows.
+template <int KT>
 __global__ void __launch_bounds__(256) to_batch_kernel(const float* __restrict__ Xb, const uint8_t* __restrict__ yb,
-                                                       int R, int64_t N, int D, int kt, float* __restrict__ X,
-                                                       uint8_t* __restrict__ y, int stride, int64_t ns)
+                                                       int R, int64_t N, int D, char* __restrict__ X, int64_t ns)
+{
+    using G = batch::Geo<KT>;
+    constexpr int kItems = kBatchStageRows * (G::kSlots + 1);
+    const int64_t total = ns * kItems;
+    for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < total;
+         o += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t st = o / kItems;
+        const int rem = (int)(o - st * kItems);
+        const int row = rem & (kBatchStageRows - 1);
+        const int slot = rem / kBatchStageRows;
+        const int64_t i = st * kBatchStageRows + row;
+        const int64_t blk = i / R;
+        const float* src = Xb + blk * D * R + (i - blk * R);  // column c at + c R
+        char* img = X + st * G::kBytes;
+        const auto value = [&](int col) { return i < N && col < D ? src[(int64_t)col * R] : 0.0f; };
+        if (slot < G::kSlots) {
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = 8 * slot + k < 16 * KT ? value(8 * slot + k) : 0.0f;
+            batch::v8bf parts[batch::kParts];
+            batch::split3(v, parts);
+            char* dst = img + row * G::kRow + (slot ^ batch::swizzle<KT>(row & (batch::kTileRows - 1))) * 16;
+#pragma unroll
+            for (int q = 0; q < batch::kParts; ++q)
+                *reinterpret_cast<batch::v8bf*>(dst + q * G::kPlane) = parts[q];
+        } else {
+            batch::v4f t;
+#pragma unroll
+            for (int k = 0; k < batch::kTail; ++k) t[k] = value(16 * KT + k);
+            *reinterpret_cast<batch::v4f*>(img + G::kTailAt + row * batch::kTail * 4) = t;
+            *reinterpret_cast<float*>(img + G::kSignAt + row * 4) = i < N && yb[i] ? -1.0f : 1.0f;
+        }
+    }
+}
+
+hipError_t launch_to_batch_layout(const DataView& src, const BatchView& dst, void* X, hipStream_t stream)
+{
+    const int64_t total = dst.ns * kBatchStageRows * (batch_cols(dst.kt) / 8 + 1);
+    if (total == 0) return hipSuccess;
+    const int64_t want = (total + 255) / 256;
+    const unsigned grid = (unsigned)(want < 65536 ? want : 65536);
+#define NUTS_LAYOUT_CASE(k)                                                                                        \
+    case k:                                                                                                        \
+        hipLaunchKernelGGL(to_batch_kernel<k>, dim3(grid), dim3(256), 0, stream, (const float*)src.X, src.y,       \
+                           rows_per_block(src), src.N, src.D, (char*)X, dst.ns);                                   \
+        break;
+    switch (dst.kt) {
+        NUTS_LAYOUT_CASE(0) NUTS_LAYOUT_CASE(1) NUTS_LAYOUT_CASE(2) NUTS_LAYOUT_CASE(3) NUTS_LAYOUT_CASE(4)
+        NUTS_LAYOUT_CASE(5) NUTS_LAYOUT_CASE(6) NUTS_LAYOUT_CASE(7) NUTS_LAYOUT_CASE(8)
+    default: return hipErrorInvalidValue;
+    }
+#undef NUTS_LAYOUT_CASE
+    return hipGetLastError();
+}
+
+__global__ void __launch_bounds__(256) to_batch_f32_kernel(const float* __restrict__ Xb,
+                                                           const uint8_t* __restrict__ yb, int R, int64_t N, int D,
+                                                           int kt, float* __restrict__ X, uint8_t* __restrict__ y,
+                                                           int stride, int64_t ns)
 {
     const int kp = batch_kp(kt);
     const int64_t per_stage = (int64_t)kBatchStageRows * stride;
@@ -39,15 +101,15 @@ __global__ void __launch_bounds__(256) to_batch_kernel(const float* __restrict__
     }
 }
 
-hipError_t launch_to_batch_layout(const DataView& src, const BatchView& dst, float* X, uint8_t* y,
-                                  hipStream_t stream)
+hipError_t launch_to_batch_layout_f32(const DataView& src, const BatchView& dst, float* X, uint8_t* y,
+                                      hipStream_t stream)
 {
-    const int64_t total = dst.ns * kBatchStageRows * dst.stride;
+    const int64_t total = dst.ns * kBatchStageRows * dst.stride32;
     if (total == 0) return hipSuccess;
     const int64_t want = (total + 255) / 256;
     const unsigned grid = (unsigned)(want < 65536 ? want : 65536);
-    hipLaunchKernelGGL(to_batch_kernel, dim3(grid), dim3(256), 0, stream, (const float*)src.X, src.y,
-                       rows_per_block(src), src.N, src.D, dst.kt, X, y, dst.stride, dst.ns);
+    hipLaunchKernelGGL(to_batch_f32_kernel, dim3(grid), dim3(256), 0, stream, (const float*)src.X, src.y,
+                       rows_per_block(src), src.N, src.D, dst.kt, X, y, dst.stride32, dst.ns);
     return hipGetLastError();
 }
 
@@ -112,6 +174,30 @@ __device__ __forceinline__ void store_partials(const BatchView& bv, WaveAcc& acc
     }
 }
 
+// The wave's positions `pos` (lane l's: l % 16) of W [.][D], zeros where !live.
+template <int KT>
+__device__ __forceinline__ void load_q(const BatchView& bv, const double* __restrict__ W, int64_t pos, bool live,
+                                       WaveQ& Q)
+{
+    const int jj = lane() >> 4;
+    const double* w = W + pos * bv.D;
+#pragma unroll
+    for (int t = 0; t < batch::Geo<KT>::kSteps; ++t) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int col = 32 * t + 8 * jj + i;
+            v[i] = (live && col < 16 * KT && col < bv.D) ? (float)w[col] : 0.0f;
+        }
+        batch::v8bf parts[batch::kParts];
+        batch::split3(v, parts);
+#pragma unroll
+        for (int q = 0; q < batch::kParts; ++q) Q.q[q][t] = parts[q];
+    }
+#pragma unroll
+    for (int k = 0; k < batch::kTail; ++k) Q.qt[k] = (live && k < bv.tc) ? (float)w[16 * KT + k] : 0.0f;
+}
+
 // ---------------------------------------------------------------------------
 // Stand-alone batched potential: pass 1 on a grid of (groups, tiles), pass 2
 // adds the partial rows of each position in group order and the prior.
@@ -122,37 +208,19 @@ __global__ void __launch_bounds__(batch::kWaves * kWave, 1) batch_pass_kernel(Ba
                                                                               float* __restrict__ P,
                                                                               double* __restrict__ L)
 {
-    __shared__ __align__(16) float xs[2 * batch::kStageBuf];
-    __shared__ __align__(16) float ys[2 * kBatchStageRows];
-    const int l = lane();
-    const int m = l & 15;
-    const int jj = l >> 4;
+    __shared__ __align__(16) char xs[2 * batch::Geo<KT>::kBytes];
     const int widx = threadIdx.x / kWave;
     const int g = blockIdx.x;
     const int t = blockIdx.y;
-    const int D = bv.D;
-    const int64_t pos = (int64_t)t * kBatchTileChains + widx * 16 + m;
-    const bool live = pos < K;
-
+    const int64_t pos = (int64_t)t * kBatchTileChains + widx * 16 + (lane() & 15);
     WaveQ Q;
-    constexpr int KP = batch::Geo<KT>::KP;
-#pragma unroll
-    for (int t = 0; t < KP; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int col = batch::e_column<KT>(t, jj, i);
-            const bool used = (col / 16) < KT && col < D;
-            Q.q[4 * t + i] = (live && used) ? (float)W[pos * D + col] : 0.0f;
-        }
-#pragma unroll
-    for (int k = 0; k < batch::kTail; ++k)
-        Q.qt[k] = (live && k < bv.tc) ? (float)W[pos * D + 16 * KT + k] : 0.0f;
+    load_q<KT>(bv, W, pos, pos < K, Q);
 
     WaveAcc acc;
     batch::zero(acc);
     int64_t h0, h1;
     batch::group_halves(bv.ns, g, groups, &h0, &h1);
-    batch::stage_loop<KT, true>(bv, h0, h1, (int)threadIdx.x, xs, ys, Q, acc);
+    batch::stage_loop<KT, true>(bv, h0, h1, (int)threadIdx.x, xs, Q, acc);
     const int64_t base = (int64_t)t * groups + g;
     store_partials<KT, false>(bv, acc, widx, pw, P + base * kBatchTileChains * pw, L + base * kBatchTileChains);
 }
@@ -288,8 +356,7 @@ __global__ void __launch_bounds__(batch::kWaves * kWave, 1) batch_ll_kernel(Batc
                                                                            float* __restrict__ Pr,
                                                                            uint8_t* __restrict__ Y, uint64_t seed)
 {
-    __shared__ __align__(16) float xs[2 * batch::kStageBuf];
-    __shared__ __align__(16) float ys[2 * kBatchStageRows];
+    __shared__ __align__(16) char xs[2 * batch::Geo<KT>::kBytes];
     __shared__ float rs[PRED ? 2 * batch::kWaves * kBatchStageRows : 1];
     const int l = lane();
     const int m = l & 15;
@@ -297,23 +364,10 @@ __global__ void __launch_bounds__(batch::kWaves * kWave, 1) batch_ll_kernel(Batc
     const int widx = threadIdx.x / kWave;
     const int g = blockIdx.x;
     const int t = blockIdx.y;
-    const int D = bv.D;
     const int64_t pos = (int64_t)t * kBatchTileChains + widx * 16 + m;
     const bool live = pos < S;
-
     WaveQ Q;
-    constexpr int KP = batch::Geo<KT>::KP;
-#pragma unroll
-    for (int c = 0; c < KP; ++c)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int col = batch::e_column<KT>(c, jj, i);
-            const bool used = (col / 16) < KT && col < D;
-            Q.q[4 * c + i] = (live && used) ? (float)W[pos * D + col] : 0.0f;
-        }
-#pragma unroll
-    for (int k = 0; k < batch::kTail; ++k)
-        Q.qt[k] = (live && k < bv.tc) ? (float)W[pos * D + 16 * KT + k] : 0.0f;
+    load_q<KT>(bv, W, pos, live, Q);
 
     double loss = 0.0;
     const int64_t st0 = (int64_t)g * bv.ns / groups;
@@ -324,7 +378,7 @@ __global__ void __launch_bounds__(batch::kWaves * kWave, 1) batch_ll_kernel(Batc
     po.s = (uint64_t)pos;
     po.N = bv.N;
     po.row0 = 0;
-    batch::stage_loop_ll<KT, PRED, SAMPLE>(bv, st0, st1, (int)threadIdx.x, xs, ys, rs, Q, live ? 1.0f : 0.0f,
+    batch::stage_loop_ll<KT, PRED, SAMPLE>(bv, st0, st1, (int)threadIdx.x, xs, rs, Q, live ? 1.0f : 0.0f,
                                            loss, Pr + (int64_t)t * bv.ns * kBatchStageRows, po);
     // the four lanes of a position hold its four row groups
     loss += __shfl_xor(loss, 16);
@@ -428,10 +482,102 @@ namespace {
 constexpr int kGroupWaves = 1 + batch::kWaves;
 constexpr int kCmdEval = 1, kCmdStop = 2, kCmdError = 3;
 
-template <int DPL>
+// What a sampler kernel's pass over the rows needs besides the exchange: its
+// LDS stages, the form in which a controller publishes a position, a worker
+// lane's share of it, and the stage loop.
+template <int KT>
+struct PassBf16 {
+    static constexpr int kLds = 2 * batch::Geo<KT>::kBytes;
+    using Q = WaveQ;
+    // published as it is: kBatchQWidth columns
+    __device__ static void put(float* dst, int col, float v)
+    {
+        __hip_atomic_store(dst + col, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // in 16-byte agent-scope loads: this lane's columns of every K-step (none
+    // past the matrix columns), then the tail
+    __device__ static void get(const float* src, Q& q)
+    {
+        const int jj = lane() >> 4;
+        const __amdgpu_buffer_rsrc_t qr = buffer_of(src);
+#pragma unroll
+        for (int t = 0; t < batch::Geo<KT>::kSteps; ++t) {
+            float v[8];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const batch::v4f f = __builtin_amdgcn_raw_buffer_load_b128(qr, (32 * t + 8 * jj + 4 * h) * 4, 0,
+                                                                           kCachePolicyAgent);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[4 * h + i] = 32 * t + 8 * jj + 4 * h + i < 16 * KT ? f[i] : 0.0f;
+            }
+            batch::v8bf parts[batch::kParts];
+            batch::split3(v, parts);
+#pragma unroll
+            for (int p = 0; p < batch::kParts; ++p) q.q[p][t] = parts[p];
+        }
+        const batch::v4f tv = __builtin_amdgcn_raw_buffer_load_b128(qr, 16 * KT * 4, 0, kCachePolicyAgent);
+#pragma unroll
+        for (int k = 0; k < batch::kTail; ++k) q.qt[k] = tv[k];
+    }
+    template <bool WORKER>
+    __device__ static void loop(const BatchView& bv, int64_t h0, int64_t h1, int tid, char* lds, const Q& q,
+                                WaveAcc& acc)
+    {
+        batch::stage_loop<KT, WORKER>(bv, h0, h1, tid, lds, q, acc);
+    }
+};
+
+template <int KT>
+struct PassF32 {
+    static constexpr int kXBytes = 2 * batch32::kStageBuf * (int)sizeof(float);
+    static constexpr int kLds = kXBytes + 2 * kBatchStageRows * (int)sizeof(float);
+    static constexpr int KP = batch32::Geo<KT>::KP;
+    using Q = batch32::WaveQ;
+    // published in the matrix-core operand order of the column contraction:
+    // lane group jj's 4 KP values contiguous, so that a worker lane reads its
+    // share with 16-byte loads; the four tail columns after the 16 KP
+    // permuted ones.  Columns of chunks past KT have a slot and hold zero.
+    __device__ static void put(float* dst, int col, float v)
+    {
+        const int c = col >> 4, g = col & 15;
+        const int i = c & 3, h = c >> 2;
+        const int f = KP == 8 ? 2 * g + h : g;
+        const int slot = (f & 3) * 4 * KP + (f >> 2) * 4 + i;
+        if (col < 16 * KP)
+            __hip_atomic_store(dst + slot, c < KT ? v : 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (col >= 16 * KT && col < 16 * KT + batch::kTail)
+            __hip_atomic_store(dst + 16 * KP + (col - 16 * KT), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ static void get(const float* src, Q& q)
+    {
+        const int jj = lane() >> 4;
+        const __amdgpu_buffer_rsrc_t qr = buffer_of(src);
+#pragma unroll
+        for (int t = 0; t < KP; ++t) {
+            const batch::v4f v = __builtin_amdgcn_raw_buffer_load_b128(qr, (jj * 4 * KP + 4 * t) * 4, 0,
+                                                                       kCachePolicyAgent);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) q.q[4 * t + i] = v[i];
+        }
+        const batch::v4f tv = __builtin_amdgcn_raw_buffer_load_b128(qr, 16 * KP * 4, 0, kCachePolicyAgent);
+#pragma unroll
+        for (int k = 0; k < batch::kTail; ++k) q.qt[k] = tv[k];
+    }
+    template <bool WORKER>
+    __device__ static void loop(const BatchView& bv, int64_t h0, int64_t h1, int tid, char* lds, const Q& q,
+                                WaveAcc& acc)
+    {
+        batch32::stage_loop<KT, WORKER>(bv, h0, h1, tid, reinterpret_cast<float*>(lds),
+                                        reinterpret_cast<float*>(lds + kXBytes), q, acc);
+    }
+};
+
+template <int KT, bool EXT>
+using SamplerPass = typename std::conditional<EXT, PassF32<KT>, PassBf16<KT>>::type;
+
+template <class Pass, int DPL>
 struct BatchShared {
-    __align__(16) float xs[2 * batch::kStageBuf];
-    __align__(16) float ys[2 * kBatchStageRows];
+    __align__(16) char xs[Pass::kLds];
     double red[kGroupWaves][(DPL + 1) * 64];
     int cmd;
 };
@@ -468,25 +614,9 @@ __device__ __forceinline__ void raise_error(const BatchCtx& c)
     if (lane() == 0) __hip_atomic_store(&c.sync->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Slot of column `col` in a published position: the matrix-core operand
-// order of the column contraction, lane group jj's 4 KP values contiguous
-// (Q.q of load_q), so that a worker lane reads its share with 16-byte loads;
-// the four tail columns after the 16 KP permuted ones.  Columns of chunks
-// past KT have a slot and hold zero.
-template <int KT>
-__device__ __forceinline__ int q_slot(int col)
-{
-    constexpr int KP = batch::Geo<KT>::KP;
-    const int c = col >> 4, g = col & 15;
-    const int i = c & 3, h = c >> 2;
-    const int f = KP == 8 ? 2 * g + h : g;
-    return (f & 3) * 4 * KP + (f >> 2) * 4 + i;
-}
-
-template <int KT, int DPL>
+template <class Pass, int DPL>
 __device__ void publish(const BatchCtx& c, unsigned long long step, const double (&q)[DPL], bool mark_done)
 {
-    constexpr int KP = batch::Geo<KT>::KP;
     const int l = lane();
     const int par = (int)(step & 1);
     const int64_t slot = (int64_t)c.t * kBatchTileChains + c.i;
@@ -496,11 +626,7 @@ __device__ void publish(const BatchCtx& c, unsigned long long step, const double
         const int col = l + 64 * m;
         float v = 0.0f;
         if (m < DPL && col < c.bv.D) v = (float)q[m < DPL ? m : 0];
-        if (col < 16 * KP)
-            __hip_atomic_store(dst + q_slot<KT>(col), (col >> 4) < KT ? v : 0.0f, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        if (col >= 16 * KT && col < 16 * KT + batch::kTail)
-            __hip_atomic_store(dst + 16 * KP + (col - 16 * KT), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        Pass::put(dst, col, v);
     }
     sampler::drain_memory_ops();
     if (mark_done) {
@@ -555,16 +681,17 @@ __device__ bool arrive_and_wait(const BatchCtx& c, unsigned long long step)
 // same workgroup barriers.  LEADER is wave 0.  Returns the command; for the
 // leader of a hosting group, `out` receives the sums for its slot: component
 // m of lane l is column l + 64 m of X^T r, component DPL of lane 0 the loss.
-template <int KT, int DPL, bool LEADER>
-__device__ int batch_collective(const BatchCtx& c, BatchShared<DPL>& sh, unsigned long long step,
+template <int KT, int DPL, bool EXT, bool LEADER>
+__device__ int batch_collective(const BatchCtx& c, BatchShared<SamplerPass<KT, EXT>, DPL>& sh, unsigned long long step,
                                 const double (&q)[DPL], bool publish_q, bool mark_done, double (&out)[DPL + 1])
 {
+    using Pass = SamplerPass<KT, EXT>;
     const int l = lane();
     const int wave = threadIdx.x / kWave;
     const int par = (int)(step & 1);
     const bool host = c.i < kBatchTileChains;
     if (LEADER) {
-        if (publish_q && host) publish<KT, DPL>(c, step, q, mark_done);
+        if (publish_q && host) publish<Pass, DPL>(c, step, q, mark_done);
         const int cmd = wait_positions(c, step);
         if (l == 0) sh.cmd = cmd;
     }
@@ -575,33 +702,19 @@ __device__ int batch_collective(const BatchCtx& c, BatchShared<DPL>& sh, unsigne
     const int64_t tile_base = ((int64_t)par * c.tiles + c.t) * c.groups;
     const int64_t rstride = (int64_t)kBatchTileChains * c.pw;
     if (LEADER) {
-        WaveQ Q;
+        typename Pass::Q Q;
         WaveAcc acc;
-        batch::stage_loop<KT, false>(c.bv, c.h0, c.h1, 0, sh.xs, sh.ys, Q, acc);
+        Pass::template loop<false>(c.bv, c.h0, c.h1, 0, sh.xs, Q, acc);
     } else {
         const int widx = wave - 1;
         const int m = l & 15;
-        const int jj = l >> 4;
         const float* qsrc = c.qbuf + ((int64_t)par * c.tiles * kBatchTileChains +
                                       (int64_t)c.t * kBatchTileChains + widx * 16 + m) * kBatchQWidth;
-        // the position in the order publish wrote it: this lane's 4 KP
-        // operand values, then the tail, in 16-byte agent-scope loads
-        WaveQ Q;
-        constexpr int KP = batch::Geo<KT>::KP;
-        const __amdgpu_buffer_rsrc_t qr = buffer_of(qsrc);
-#pragma unroll
-        for (int t = 0; t < KP; ++t) {
-            const batch::v4f v = __builtin_amdgcn_raw_buffer_load_b128(qr, (jj * 4 * KP + 4 * t) * 4, 0,
-                                                                       kCachePolicyAgent);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) Q.q[4 * t + i] = v[i];
-        }
-        const batch::v4f tv = __builtin_amdgcn_raw_buffer_load_b128(qr, 16 * KP * 4, 0, kCachePolicyAgent);
-#pragma unroll
-        for (int k = 0; k < batch::kTail; ++k) Q.qt[k] = tv[k];
+        typename Pass::Q Q;
+        Pass::get(qsrc, Q);
         WaveAcc acc;
         batch::zero(acc);
-        batch::stage_loop<KT, true, true>(c.bv, c.h0, c.h1, (int)threadIdx.x - kWave, sh.xs, sh.ys, Q, acc);
+        Pass::template loop<true>(c.bv, c.h0, c.h1, (int)threadIdx.x - kWave, sh.xs, Q, acc);
         store_partials<KT, true>(c.bv, acc, widx, c.pw, c.P + (tile_base + c.i) * rstride,
                                  c.L + (tile_base + c.i) * kBatchTileChains);
         sampler::drain_memory_ops();
@@ -690,7 +803,7 @@ struct BatchEval {
     // extended features has the room (see EdgeNodes and batch_edge_nodes)
     static constexpr bool kNodesInLds = DPL >= 3 && !EXT;
     BatchCtx c;
-    BatchShared<DPL>* sh;
+    BatchShared<SamplerPass<KT, EXT>, DPL>* sh;
     double inv_s2, prior_const;
     unsigned long long step;
     bool abort;
@@ -702,7 +815,7 @@ struct BatchEval {
     __device__ void eval(const double (&q)[DPL], double& U, double (&g)[DPL])
     {
         double r[DPL + 1];
-        const int cmd = batch_collective<KT, DPL, true>(c, *sh, step, q, true, false, r);
+        const int cmd = batch_collective<KT, DPL, EXT, true>(c, *sh, step, q, true, false, r);
         step++;
         const int l = lane();
         if (cmd != kCmdEval) {
@@ -730,7 +843,7 @@ struct BatchEval {
         for (int m = 0; m < DPL; ++m) q[m] = 0.0;
         bool first = true;
         for (;;) {
-            const int cmd = batch_collective<KT, DPL, true>(c, *sh, step, q, publish_q, first, r);
+            const int cmd = batch_collective<KT, DPL, EXT, true>(c, *sh, step, q, publish_q, first, r);
             first = false;
             step++;
             if (cmd != kCmdEval) break;
@@ -745,7 +858,7 @@ __global__ void __launch_bounds__(kGroupWaves * kWave, 1) sampler_batch_kernel(S
                                                                               BatchSync* sync)
 {
     extern __shared__ double lds[];  // the controller's checkpoint array
-    __shared__ BatchShared<DPL> sh;
+    __shared__ BatchShared<SamplerPass<KT, EXT>, DPL> sh;
     BatchCtx c;
     c.bv = bv;
     c.tiles = tiles;
@@ -776,7 +889,7 @@ __global__ void __launch_bounds__(kGroupWaves * kWave, 1) sampler_batch_kernel(S
 #pragma unroll
         for (int m = 0; m < DPL; ++m) q[m] = 0.0;
         for (unsigned long long step = 0;; ++step)
-            if (batch_collective<KT, DPL, false>(c, sh, step, q, false, false, r) != kCmdEval) break;
+            if (batch_collective<KT, DPL, EXT, false>(c, sh, step, q, false, false, r) != kCmdEval) break;
     }
 }
 

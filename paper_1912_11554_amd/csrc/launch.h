@@ -193,27 +193,33 @@ GridPlan plan_grid_sampler(const DataView& dv, int max_depth, int sub_merge, int
 // positions as one contraction E = X Q (N x D by D x K) on the matrix cores,
 // the row terms on E, then G = X^T R (D x N by N x K).
 //
-// Layout: stages of 64 rows; a stage is 64 rows of `stride` floats, row r of
-// stage s at (s * 64 + r) * stride.  The first 16 kp floats of a row
-// (kp = kt rounded up to a multiple of 4) hold the columns that feed the
-// matrix cores, permuted: slot g * kp + t holds column 16 t + g (g < 16,
-// t < kp; zero for t >= kt), so that the 16-column chunks t of one column
-// residue g are contiguous.  The last 4 floats hold the tail: up to four more
-// columns (16 kt .. 16 kt + 3) handled on the vector ALUs.  Entries past N
-// or past D are zero.  y is one byte per row, 0 past N (padding rows: zero X,
-// label 0).
+// Layout: stages of 64 rows, each an image of batch_stage_bytes(kt) bytes that
+// the kernels copy to LDS as it is: the first 16 kt columns as three planes of
+// bf16 parts whose sum is the fp32 value (batch_cols columns a row, zero past
+// the last), then the tail, up to four more columns (16 kt .. 16 kt + 3)
+// handled on the vector ALUs, as four floats a row, then one float a row, the
+// label's sign 1 - 2 y.  Rows past N and columns past D are zero (label 0).
 struct BatchView {
-    const float* X;
-    const uint8_t* y;
+    const void* X;
     int64_t N;
     int D;
     int kt;          // 16-column chunks on the matrix cores
     int tc;          // tail columns on the vector ALUs (0..4)
-    int stride;      // 16 kp + 4 floats
     int64_t ns;      // stages: ceil(N / 64)
+    // the fp32 layout of batch_f32.h, for the sampler kernels with the
+    // optional features; null until such a launch
+    const float* X32;
+    const uint8_t* y32;
+    int stride32;    // floats a row
 };
-__host__ __device__ inline int batch_kp(int kt) { return (kt + 3) / 4 * 4; }
 constexpr int kBatchStageRows = 64;
+__host__ __device__ inline int batch_kp(int kt) { return (kt + 3) / 4 * 4; }
+inline int batch_stride32(int kt) { return 16 * batch_kp(kt) + 4; }
+__host__ __device__ constexpr int batch_cols(int kt) { return kt == 0 ? 0 : kt <= 2 ? 32 : kt <= 4 ? 64 : 128; }
+__host__ __device__ constexpr int batch_stage_bytes(int kt)
+{
+    return kBatchStageRows * (3 * 2 * batch_cols(kt) + 4 * 4 + 4);
+}
 constexpr int kBatchMaxKT = 8;          // D <= 132
 constexpr int kBatchTileChains = 128;   // chains (positions) per tile: 8 waves x 16
 constexpr int kBatchMaxTiles = 2;       // tiles per sampler launch
@@ -233,10 +239,12 @@ inline bool batch_shape(int D, int* kt, int* tc)
     return true;
 }
 
-// Fill X/y of the batch layout from the column-block layout of `src` (fp32,
-// one data set).
-hipError_t launch_to_batch_layout(const DataView& src, const BatchView& dst, float* X, uint8_t* y,
-                                  hipStream_t stream);
+// Fill the stages of the batch layout from the column-block layout of `src`
+// (fp32, one data set).
+hipError_t launch_to_batch_layout(const DataView& src, const BatchView& dst, void* X, hipStream_t stream);
+// The same for the fp32 layout.
+hipError_t launch_to_batch_layout_f32(const DataView& src, const BatchView& dst, float* X, uint8_t* y,
+                                      hipStream_t stream);
 
 // Workspace of the batched potential: fp32 partial rows P[T][G][128][pw]
 // and fp64 loss partials L[T][G][128], T = ceil(K / 128) tiles of G groups.
