@@ -747,7 +747,7 @@ int nuts_data_potential_grad_batched(nuts_handle* h, const nuts_data* d, double 
     HIP_TRY(h, stage_in(W, (size_t)K * D * 8, wt, &Wd, h->stream));
     HIP_TRY(h, stage_out(out_U, (size_t)K * 8, ut, &Ud));
     HIP_TRY(h, stage_out(out_grad, (size_t)K * D * 8, gt, &Gd));
-    const BatchPlan plan = plan_batch_potential(d->batch, K, h->num_cu);
+    const BatchPlan plan = plan_batch_potential(d->batch, K, h->num_cu, true);
     const size_t rows = (size_t)plan.tiles * plan.groups * kBatchTileChains;
     const size_t pbytes = align256(rows * plan.pw * sizeof(float));
     void* scratch = nullptr;
@@ -788,7 +788,7 @@ int nuts_data_log_likelihood(nuts_handle* h, const nuts_data* d, const double* W
     if (mfma) {
         const int rc = ensure_batch_layout(h, d);
         if (rc != NUTS_OK) return rc;
-        const BatchPlan plan = plan_batch_potential(d->batch, S, h->num_cu);
+        const BatchPlan plan = plan_batch_potential(d->batch, S, h->num_cu, false);
         const size_t lbytes = align256((size_t)plan.tiles * plan.groups * kBatchTileChains * sizeof(double));
         const size_t rbytes = out_pred_mean ? (size_t)plan.tiles * d->batch.ns * kBatchStageRows * sizeof(float) : 0;
         void* scratch = nullptr;
@@ -841,7 +841,7 @@ int nuts_data_posterior_predictive(nuts_handle* h, const nuts_data* d, const dou
     HIP_TRY(h, stage_out(out_y, (size_t)S * N, yt, &Yd));
     const int rc = ensure_batch_layout(h, d);
     if (rc != NUTS_OK) return rc;
-    const BatchPlan plan = plan_batch_potential(d->batch, S, h->num_cu);
+    const BatchPlan plan = plan_batch_potential(d->batch, S, h->num_cu, false);
     const size_t lbytes = align256((size_t)plan.tiles * plan.groups * kBatchTileChains * sizeof(double));
     void* scratch = nullptr;
     HIP_TRY(h, handle_scratch(h, lbytes, &scratch));

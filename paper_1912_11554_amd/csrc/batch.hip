@@ -290,12 +290,20 @@ __global__ void __launch_bounds__(kFinishWaves * kWave) batch_finish_kernel(int 
 
 }  // namespace
 
-BatchPlan plan_batch_potential(const BatchView& bv, int64_t K, int num_cu)
+BatchPlan plan_batch_potential(const BatchView& bv, int64_t K, int num_cu, bool gradient)
 {
     BatchPlan p;
     p.tiles = (int)((K + kBatchTileChains - 1) / kBatchTileChains);
-    // one group per CU (a group's two LDS stages take most of a CU's LDS)
+    // as many groups as run at once: one per CU where its two LDS stages take
+    // most of a CU's LDS, two up to 68 columns (a third of it, and at most
+    // 128 registers) for the passes without the gradient, up to 36 with it
+    // (500 draws over 581,012 x 55: log-likelihood 242 us with one, 233 with
+    // two, predictive samples 761 and 669; gradients of 512 positions on
+    // 400,000 x 9: 237 and 201, of 256 on 200,000 x 64: 102 and 111, whose
+    // partial rows weigh more), and only where each still takes four stages
+    // (100 draws over 20,000 x 20, one stage a group: 37.6 us and 39.4)
     int64_t g = (int64_t)num_cu / p.tiles;
+    if (bv.kt <= (gradient ? 2 : 4) && bv.ns >= 8 * g) g = 2 * (int64_t)num_cu / p.tiles;
     if (g > bv.ns) g = bv.ns;
     if (g < 1) g = 1;
     p.groups = (int)g;
@@ -378,6 +386,7 @@ __global__ void __launch_bounds__(batch::kWaves * kWave, 1) batch_ll_kernel(Batc
     po.s = (uint64_t)pos;
     po.N = bv.N;
     po.row0 = 0;
+    po.words = (bv.N & 3) == 0 && (reinterpret_cast<uintptr_t>(Y) & 3) == 0;
     batch::stage_loop_ll<KT, PRED, SAMPLE>(bv, st0, st1, (int)threadIdx.x, xs, rs, Q, live ? 1.0f : 0.0f,
                                            loss, Pr + (int64_t)t * bv.ns * kBatchStageRows, po);
     // the four lanes of a position hold its four row groups
@@ -386,17 +395,40 @@ __global__ void __launch_bounds__(batch::kWaves * kWave, 1) batch_ll_kernel(Batc
     if (jj == 0) L[((int64_t)t * groups + g) * kBatchTileChains + widx * 16 + m] = loss;
 }
 
-// ll[s] = -(sum over groups of the loss partials - the padding rows' ln 2).
-__global__ void __launch_bounds__(64) batch_ll_finish_kernel(int64_t S, int groups, int npad,
-                                                            const double* __restrict__ L,
-                                                            double* __restrict__ out_ll)
+// ll[s] = -(sum over groups of the loss partials - the padding rows' ln 2).  64
+// draws a block; wave w takes groups w, w + 4, .. in order, eight loads in
+// flight, and the four waves' sums are added in wave order.  (One thread a
+// draw reading its groups one after another took 17 us for 500 draws and 64
+// groups, of a 251 us pass.)
+__global__ void __launch_bounds__(kFinishWaves * kWave) batch_ll_finish_kernel(int64_t S, int groups, int npad,
+                                                                              const double* __restrict__ L,
+                                                                              double* __restrict__ out_ll)
 {
-    const int64_t s = (int64_t)blockIdx.x * 64 + threadIdx.x;
-    if (s >= S) return;
+    __shared__ double red[kFinishWaves][kWave];
+    const int l = lane();
+    const int wave = threadIdx.x / kWave;
+    const int64_t s = (int64_t)blockIdx.x * kWave + l;
     const int64_t t = s / kBatchTileChains;
     const double* src = L + t * groups * kBatchTileChains + s % kBatchTileChains;
     double tot = 0.0;
-    for (int g = 0; g < groups; ++g) tot += src[(int64_t)g * kBatchTileChains];
+    if (s < S) {
+        constexpr int U = 8;
+        int g = wave;
+        for (; g + (U - 1) * kFinishWaves < groups; g += U * kFinishWaves) {
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = src[(int64_t)(g + u * kFinishWaves) * kBatchTileChains];
+#pragma unroll
+            for (int u = 0; u < U; ++u) tot += v[u];
+        }
+        for (; g < groups; g += kFinishWaves) tot += src[(int64_t)g * kBatchTileChains];
+    }
+    red[wave][l] = tot;
+    __syncthreads();
+    if (wave != 0 || s >= S) return;
+    tot = 0.0;
+#pragma unroll
+    for (int w = 0; w < kFinishWaves; ++w) tot += red[w][l];
     out_ll[s] = -(tot - (double)npad * (double)batch::kLn2f);
 }
 
@@ -445,8 +477,8 @@ hipError_t launch_batch_log_likelihood(const BatchView& bv, const double* W, int
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (out_y) return hipSuccess;  // the predictive samples only
-    hipLaunchKernelGGL(batch_ll_finish_kernel, dim3((unsigned)((S + 63) / 64)), dim3(64), 0, stream, S, plan.groups,
-                       (int)(bv.ns * kBatchStageRows - bv.N), L, out_ll);
+    hipLaunchKernelGGL(batch_ll_finish_kernel, dim3((unsigned)((S + kWave - 1) / kWave)),
+                       dim3(kFinishWaves * kWave), 0, stream, S, plan.groups, (int)(bv.ns * kBatchStageRows - bv.N), L, out_ll);
     e = hipGetLastError();
     if (e != hipSuccess || !pred) return e;
     const int64_t want = (bv.N + 255) / 256;

@@ -253,7 +253,8 @@ struct BatchPlan {
     int groups;   // per tile
     int pw;       // 64 * ceil(D / 64)
 };
-BatchPlan plan_batch_potential(const BatchView& bv, int64_t K, int num_cu);
+// (gradient: for launch_batch_potential, else for launch_batch_log_likelihood)
+BatchPlan plan_batch_potential(const BatchView& bv, int64_t K, int num_cu, bool gradient);
 hipError_t launch_batch_potential(const BatchView& bv, double prior_scale, const double* W, int64_t K,
                                   const BatchPlan& plan, float* P, double* L, double* out_U, double* out_grad,
                                   hipStream_t stream);

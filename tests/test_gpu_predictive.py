@@ -52,6 +52,29 @@ def test_matches_oracle(sampler, orc, N, D, S):
     d.free()
 
 
+# rows stored four at a time or one by one, a remainder of a stage, one group a
+# CU and two; X W on both sides of sigma(0) = 1/2, of 1 in fp32 and of 0
+@pytest.mark.parametrize("N,D,S", [(1, 2, 129), (66, 4, 3), (131071, 5, 2), (131072, 5, 2), (131076, 36, 3),
+                                   (131074, 68, 2), (40004, 69, 1)])
+def test_words_and_groups(sampler, orc, N, D, S):
+    X, y, _ = workloads.make_logistic(N, D, w_scale=0.5, key=[96, N * 1000 + D], dtype="f32")
+    X[::3] = 0.0
+    X[1::5] *= 100.0
+    W = np.random.default_rng([95, S]).normal(0.0, 0.6, size=(S, D))
+    say("predictive words", N, D, S)
+    d = sampler.data(X, y)
+    yy = d.posterior_predictive(W, seed=77)
+    _check(yy, X, W, 77, orc)
+    # the log-likelihood of the same products: fp32 row losses (3e-8 each of
+    # their size) under the products' 1e-6 (1 + sum_j |x_ij w_j|)
+    ll = d.log_likelihood(W)[0]
+    X64 = X.astype(np.float64)
+    t = (1.0 - 2.0 * y)[None, :] * (W @ X64.T)
+    bound = (1e-6 * (1.0 + np.abs(W) @ np.abs(X64).T)).sum(axis=1) + 1e-6 * np.abs(t).sum(axis=1)
+    assert np.all(np.abs(ll + np.logaddexp(0.0, t).sum(axis=1)) <= bound)
+    d.free()
+
+
 def test_full_size_sampled_draws(sampler, orc):
     # the covtype-shaped fp32 set with 500 draws (four tiles of 128), five
     # draws checked against the oracle over every row
