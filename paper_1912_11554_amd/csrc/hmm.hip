@@ -16,15 +16,13 @@ static hipError_t potential_launch(const HmmView& hv, const double* Q, int64_t n
 {
     const int D = hmm_dim(hv.K, hv.V);
     const hmm::HmmLds L = hmm::hmm_lds(K, hv.V, hv.T, hv.Tsup, D, 1, 0);
-    const int cpg = hmm::hmm_chains_per_group(L, n);
-    if (cpg == 0) return hipErrorInvalidValue;
-    const size_t lds = (size_t)cpg * L.wave * sizeof(double);
+    const size_t lds = (size_t)L.wave * sizeof(double);
+    if (lds > sampler::kMaxGroupLds) return hipErrorInvalidValue;
     const void* k = (const void*)hmm::hmm_potential_kernel<K>;
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    const unsigned grid = (unsigned)((n + cpg - 1) / cpg);
-    hipLaunchKernelGGL((hmm::hmm_potential_kernel<K>), dim3(grid), dim3(hmm::kHmmChainsPerGroup * kWave), lds,
-                       stream, hv, D, Q, n, out_U, out_grad, cpg);
+    hipLaunchKernelGGL((hmm::hmm_potential_kernel<K>), dim3((unsigned)n), dim3(kWave), lds, stream, hv, D, Q,
+                       out_U, out_grad);
     return hipGetLastError();
 }
 

@@ -26,20 +26,28 @@
 // distribution a_s to a_{s+1} proportional to a_s M_s, M_s = Theta
 // diag(phi(w_s)) (diag(phi(w_0)) alone when no state is observed: the
 // chain then starts from the uniform distribution).
-//   1. Each lane multiplies its steps' matrices, rescaled by powers of two
-//      (exact), so only directions carry rounding.
+//   1. Each lane multiplies its steps' matrices and rescales the product by
+//      a power of two (exact), so only directions carry rounding.
 //   2. A prefix product over the lanes gives each lane the direction of its
-//      first forward vector, a suffix product that of its last backward
-//      vector.
-//   3. Each lane re-runs the scaled forward recursion over its steps (a
-//      normalised to sum 1, c_s its normaliser, log p = sum_s log c_s), then
-//      the scaled backward recursion (b_{s-1} = M_s b_s / c_s, starting
-//      from the direction of step 2 with a_{s+1} . b_s = 1), adding the
-//      expected transition counts a_s(j) Theta_jk phi_k(w_s) b_s(k) / c_s
-//      in registers and storing the occupancies a_{s+1}(k) b_s(k) in LDS,
+//      first forward vector.  The prefix's windows, applied to vectors, also
+//      give that of its last backward vector.
+//   3. Each lane re-runs the forward recursion over its steps from a vector of
+//      sum 1 (the last vector's sum is the lane's factor of p), then the
+//      backward recursion (b_{s-1} = M_s b_s, starting from the direction of
+//      step 2 with a_{s+1} . b_s = 1, which then holds at every step), adding
+//      the expected transition counts a_s(j) Theta_jk phi_k(w_s) b_s(k) in
+//      registers and storing the occupancies a_{s+1}(k) b_s(k) in LDS,
 //      grouped by symbol.
 //   4. Emission lanes add their symbol's run of occupancies (in time order),
 //      transition lanes take wave sums of the transition counts.
+//
+// Range.  The direct form of steps 1 to 3 runs where every entry is at least
+// e^-30: a lane's unscaled products of eight steps then stay above e^-540, and
+// its scaled product has no entry more than 2^130 below its largest.  Products
+// over lanes are not rescaled; where their end is above 2^-300, what may have
+// underflowed on the way is below 2^-490 of any of its components.  Otherwise
+// (extreme positions, NaN) the careful form rescales after every product and
+// normalises every step.
 #pragma once
 
 #include "sampler_impl.h"
@@ -49,8 +57,9 @@ namespace hmm {
 
 using sampler::run_chain;
 
-constexpr int kHmmChainsPerGroup = 4;
 constexpr double kLn2 = 0.69314718055994530942;
+constexpr double kDirectLog = -30.0;
+constexpr double kDirectMin = 0x1p-300;
 
 // Orders this wave's LDS stores before its later LDS loads of other lanes'
 // data (and the loads before later stores).
@@ -93,18 +102,43 @@ __device__ __forceinline__ void unit_scale(double (&P)[K][K])
         for (int c = 0; c < K; ++c) P[r][c] = ldexp(P[r][c], -e);
 }
 
+// The same for a vector.
 template <int K>
-__device__ __forceinline__ void mat_mul(const double (&A)[K][K], const double (&B)[K][K], double (&C)[K][K])
+__device__ __forceinline__ void unit_scale_vec(double (&v)[K])
+{
+    double mx = v[0];
+#pragma unroll
+    for (int k = 1; k < K; ++k) mx = fmax(mx, v[k]);
+    int e = 0;
+    (void)frexp(mx, &e);
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = ldexp(v[k], -e);
+}
+
+// t = A v
+template <int K>
+__device__ __forceinline__ void mat_vec(const double (&A)[K][K], const double (&v)[K], double (&t)[K])
 {
 #pragma unroll
-    for (int r = 0; r < K; ++r)
+    for (int j = 0; j < K; ++j) {
+        double s = 0.0;
 #pragma unroll
-        for (int c = 0; c < K; ++c) {
-            double s = 0.0;
+        for (int k = 0; k < K; ++k) s += A[j][k] * v[k];
+        t[j] = s;
+    }
+}
+
+// t = v A
+template <int K>
+__device__ __forceinline__ void vec_mat(const double (&v)[K], const double (&A)[K][K], double (&t)[K])
+{
 #pragma unroll
-            for (int j = 0; j < K; ++j) s += A[r][j] * B[j][c];
-            C[r][c] = s;
-        }
+    for (int k = 0; k < K; ++k) {
+        double s = 0.0;
+#pragma unroll
+        for (int j = 0; j < K; ++j) s += v[j] * A[j][k];
+        t[k] = s;
+    }
 }
 
 // Sums over the wave of N values per lane at once (a reduce-scatter
@@ -160,7 +194,7 @@ __host__ __device__ inline int scatter_lane(int e, int C)
     return lanebits;
 }
 
-// LDS of one wave, in doubles: the checkpoint array S, the occupancies
+// LDS of one wave (a group of its own), in doubles: the checkpoint array S, the occupancies
 // (Tu x K, symbol-sorted; first used to sort the symbols), the emission
 // table (V x K), the row table (2K rows of row_width, zero-padded).
 struct HmmLds {
@@ -361,6 +395,211 @@ struct HmmEval {
         return acc;
     }
 
+    // Steps 1 to 3 from the rows' probabilities (th, and phi in LDS): the
+    // expected transition counts of this lane's steps, its part of log p, and
+    // the occupancies in LDS.  Returns false (the same on every lane, with
+    // nothing stored) where the direct form cannot vouch for its range.
+    template <bool CAREFUL>
+    __device__ __forceinline__ bool recursions(const double (&th)[K][K], double (&xi)[K][K], double& logp)
+    {
+        const int l = lane();
+        // only the sequence's first step can be without a transition
+        const bool diag0 = no_transition0 && l == 0;
+
+        // 1. this lane's product of step matrices
+        double P[K][K];
+        set_identity<K>(P);
+#pragma unroll
+        for (int i = 0; i < kHmmSteps; ++i) {
+            if (i < ns) {
+                const double* f = phi + (sp[i] & 255) * K;
+                if (i == 0) {
+#pragma unroll
+                    for (int r = 0; r < K; ++r)
+#pragma unroll
+                        for (int k = 0; k < K; ++k) P[r][k] = (diag0 ? (r == k ? 1.0 : 0.0) : th[r][k]) * f[k];
+                } else {
+#pragma unroll
+                    for (int r = 0; r < K; ++r) {
+                        double n[K];
+#pragma unroll
+                        for (int k = 0; k < K; ++k) {
+                            double s = 0.0;
+#pragma unroll
+                            for (int j = 0; j < K; ++j) s += P[r][j] * th[j][k];
+                            n[k] = s * f[k];
+                        }
+#pragma unroll
+                        for (int k = 0; k < K; ++k) P[r][k] = n[k];
+                    }
+                }
+                if constexpr (CAREFUL) unit_scale<K>(P);
+            }
+        }
+        if constexpr (!CAREFUL) unit_scale<K>(P);
+
+        // 2. P becomes the product of the lanes l - 2 off + 1 .. l, window by
+        // window; beside it b, the product of the lanes l + 1 .. l + off (up
+        // to the last) times ones, doubles its reach by the window that ends
+        // `off` lanes on.  The last window is applied to vectors alone.
+        double b[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            double s = 0.0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) s += P[j][k];
+            s = __shfl_down(s, 1);
+            b[j] = l < kWave - 1 ? s : 1.0;
+        }
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            double t[K];
+            mat_vec<K>(P, b, t);
+            if constexpr (CAREFUL) unit_scale_vec<K>(t);
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                const double s = __shfl_down(t[j], off);
+                b[j] = l + off < kWave ? s : b[j];
+            }
+            if (off == kWave / 2) break;
+            double O[K][K];
+#pragma unroll
+            for (int r = 0; r < K; ++r)
+#pragma unroll
+                for (int k = 0; k < K; ++k) O[r][k] = __shfl_up(P[r][k], off);
+            if (l >= off) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    double n[K];
+#pragma unroll
+                    for (int r = 0; r < K; ++r) {
+                        double s = 0.0;
+#pragma unroll
+                        for (int j = 0; j < K; ++j) s += O[r][j] * P[j][k];
+                        n[r] = s;
+                    }
+#pragma unroll
+                    for (int r = 0; r < K; ++r) P[r][k] = n[r];
+                }
+                if constexpr (CAREFUL) unit_scale<K>(P);
+            }
+        }
+        // the forward start: init times the product of lanes 0 .. l - 1
+        double alpha[K];
+        double st = 0.0;
+        {
+            double wv[K], up[K];
+            vec_mat<K>(init, P, wv);
+#pragma unroll
+            for (int k = 0; k < K; ++k) up[k] = __shfl_up(wv[k], kWave / 2);
+            if constexpr (CAREFUL) unit_scale_vec<K>(up);
+            if (l >= kWave / 2) vec_mat<K>(up, P, wv);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                wv[k] = __shfl_up(wv[k], 1);
+                st += wv[k];
+            }
+            if constexpr (!CAREFUL) {
+                double bs = 0.0;
+#pragma unroll
+                for (int k = 0; k < K; ++k) bs += b[k];
+                if (__any(!(l == 0 || st >= kDirectMin) || !(bs >= kDirectMin))) return false;
+            }
+            const double r = recip(st);
+#pragma unroll
+            for (int k = 0; k < K; ++k) alpha[k] = l == 0 ? init[k] : wv[k] * r;
+        }
+
+        // 3a. forward over this lane's steps
+        double ah[kHmmSteps][K];            // a_s before each step
+        double rc[CAREFUL ? kHmmSteps : 1];  // 1 / c_s
+        double lm = 1.0;                    // product of the c_s as mantissa and exponent
+        int le = 0;
+#pragma unroll
+        for (int i = 0; i < kHmmSteps; ++i) {
+            if (i < ns) {
+                const double* f = phi + (sp[i] & 255) * K;
+                double u[K], c = 0.0;
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    ah[i][k] = alpha[k];
+                    double s = 0.0;
+#pragma unroll
+                    for (int j = 0; j < K; ++j) s += alpha[j] * th[j][k];
+                    u[k] = (i == 0 && diag0 ? alpha[k] : s) * f[k];
+                    c += u[k];
+                }
+                if constexpr (CAREFUL) {
+                    const double r = recip(c);
+                    rc[i] = r;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) alpha[k] = u[k] * r;
+                    int e = 0;
+                    lm = frexp(lm * c, &e);
+                    le += e;
+                } else {
+#pragma unroll
+                    for (int k = 0; k < K; ++k) alpha[k] = u[k];
+                }
+            }
+        }
+        if constexpr (!CAREFUL) {
+            lm = 0.0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) lm += alpha[k];
+        }
+        logp = ns > 0 ? log(lm) + (double)le * kLn2 : 0.0;
+
+        // 3b. backward, expected counts
+        double beta[K];
+        {
+            const bool last = s0 + ns == Tu;
+            double d = 0.0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) d += alpha[k] * (last ? 1.0 : b[k]);
+            const double r = recip(d);
+#pragma unroll
+            for (int k = 0; k < K; ++k) beta[k] = last ? (CAREFUL ? 1.0 : r) : b[k] * r;
+        }
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+#pragma unroll
+            for (int k = 0; k < K; ++k) xi[j][k] = 0.0;
+#pragma unroll
+        for (int i = kHmmSteps - 1; i >= 0; --i) {
+            if (i < ns) {
+                const double* f = phi + (sp[i] & 255) * K;
+                double* gp = gam + (sp[i] >> 8) * K;
+                double v[K];
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    gp[k] = alpha[k] * beta[k];
+                    v[k] = f[k] * beta[k];
+                    if constexpr (CAREFUL) v[k] *= rc[i];
+                }
+                if (i > 0 || !diag0) {
+#pragma unroll
+                    for (int j = 0; j < K; ++j)
+#pragma unroll
+                        for (int k = 0; k < K; ++k) xi[j][k] += ah[i][j] * v[k];
+                }
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                    double s = 0.0;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) s += th[j][k] * v[k];
+                    beta[j] = s;
+                    alpha[j] = ah[i][j];
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+#pragma unroll
+            for (int k = 0; k < K; ++k) xi[j][k] *= th[j][k];
+        return true;
+    }
+
     __device__ void eval(const double (&q)[1], double& U, double (&g)[1])
     {
         const int l = lane();
@@ -388,181 +627,10 @@ struct HmmEval {
         }
         wave_lds_sync();
 
-        // 1. this lane's product of step matrices
-        double P[K][K];
-        set_identity<K>(P);
-#pragma unroll
-        for (int i = 0; i < kHmmSteps; ++i) {
-            if (i < ns) {
-                const double* f = phi + (sp[i] & 255) * K;
-                const bool diag = no_transition0 && s0 + i == 0;
-                double N[K][K];
-#pragma unroll
-                for (int r = 0; r < K; ++r)
-#pragma unroll
-                    for (int k = 0; k < K; ++k) {
-                        double s = 0.0;
-#pragma unroll
-                        for (int j = 0; j < K; ++j) s += P[r][j] * th[j][k];
-                        N[r][k] = (diag ? P[r][k] : s) * f[k];
-                    }
-                unit_scale<K>(N);
-#pragma unroll
-                for (int r = 0; r < K; ++r)
-#pragma unroll
-                    for (int k = 0; k < K; ++k) P[r][k] = N[r][k];
-            }
-        }
-        double Pown[K][K];
-#pragma unroll
-        for (int r = 0; r < K; ++r)
-#pragma unroll
-            for (int k = 0; k < K; ++k) Pown[r][k] = P[r][k];
-
-        // 2a. inclusive prefix product over lanes; the forward start of lane
-        // l is init times the product of lanes 0 .. l-1, normalised
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            double O[K][K], N[K][K];
-#pragma unroll
-            for (int r = 0; r < K; ++r)
-#pragma unroll
-                for (int k = 0; k < K; ++k) O[r][k] = __shfl_up(P[r][k], off);
-            if (l >= off) {
-                mat_mul<K>(O, P, N);
-                unit_scale<K>(N);
-#pragma unroll
-                for (int r = 0; r < K; ++r)
-#pragma unroll
-                    for (int k = 0; k < K; ++k) P[r][k] = N[r][k];
-            }
-        }
-        double alpha[K];
-        {
-            double wv[K];
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                double s = 0.0;
-#pragma unroll
-                for (int j = 0; j < K; ++j) s += init[j] * P[j][k];
-                wv[k] = s;
-            }
-            double st = 0.0;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                wv[k] = __shfl_up(wv[k], 1);
-                st += wv[k];
-            }
-            const double r = recip(st);
-#pragma unroll
-            for (int k = 0; k < K; ++k) alpha[k] = l == 0 ? init[k] : wv[k] * r;
-        }
-
-        // 2b. inclusive suffix product; the backward direction at the last
-        // step of lane l is the product of lanes l+1 .. 63 times ones
-#pragma unroll
-        for (int r = 0; r < K; ++r)
-#pragma unroll
-            for (int k = 0; k < K; ++k) P[r][k] = Pown[r][k];
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            double O[K][K], N[K][K];
-#pragma unroll
-            for (int r = 0; r < K; ++r)
-#pragma unroll
-                for (int k = 0; k < K; ++k) O[r][k] = __shfl_down(P[r][k], off);
-            if (l + off < kWave) {
-                mat_mul<K>(P, O, N);
-                unit_scale<K>(N);
-#pragma unroll
-                for (int r = 0; r < K; ++r)
-#pragma unroll
-                    for (int k = 0; k < K; ++k) P[r][k] = N[r][k];
-            }
-        }
-        double bdir[K];
-#pragma unroll
-        for (int j = 0; j < K; ++j) {
-            double s = 0.0;
-#pragma unroll
-            for (int k = 0; k < K; ++k) s += P[j][k];
-            bdir[j] = __shfl_down(s, 1);
-        }
-
-        // 3a. scaled forward over this lane's steps
-        double ah[kHmmSteps][K];  // a_s before each step
-        double rc[kHmmSteps];     // 1 / c_s
-        double lm = 1.0;          // product of the c_s as mantissa and exponent
-        int le = 0;
-#pragma unroll
-        for (int i = 0; i < kHmmSteps; ++i) {
-            if (i < ns) {
-                const double* f = phi + (sp[i] & 255) * K;
-                const bool diag = no_transition0 && s0 + i == 0;
-                double u[K], c = 0.0;
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    ah[i][k] = alpha[k];
-                    double s = 0.0;
-#pragma unroll
-                    for (int j = 0; j < K; ++j) s += alpha[j] * th[j][k];
-                    u[k] = (diag ? alpha[k] : s) * f[k];
-                    c += u[k];
-                }
-                const double r = recip(c);
-                rc[i] = r;
-#pragma unroll
-                for (int k = 0; k < K; ++k) alpha[k] = u[k] * r;
-                int e = 0;
-                lm = frexp(lm * c, &e);
-                le += e;
-            }
-        }
-        const double logp = ns > 0 ? log(lm) + (double)le * kLn2 : 0.0;
-
-        // 3b. scaled backward, expected counts
-        double beta[K];
-        {
-            const bool last = s0 + ns == Tu;
-            double d = 0.0;
-#pragma unroll
-            for (int k = 0; k < K; ++k) d += alpha[k] * bdir[k];
-            const double r = recip(d);
-#pragma unroll
-            for (int k = 0; k < K; ++k) beta[k] = last ? 1.0 : bdir[k] * r;
-        }
-        double xi[K][K];
-#pragma unroll
-        for (int j = 0; j < K; ++j)
-#pragma unroll
-            for (int k = 0; k < K; ++k) xi[j][k] = 0.0;
-#pragma unroll
-        for (int i = kHmmSteps - 1; i >= 0; --i) {
-            if (i < ns) {
-                const double* f = phi + (sp[i] & 255) * K;
-                double* gp = gam + (sp[i] >> 8) * K;
-                double v[K];
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    gp[k] = alpha[k] * beta[k];
-                    v[k] = f[k] * beta[k] * rc[i];
-                }
-                if (!(no_transition0 && s0 + i == 0)) {
-#pragma unroll
-                    for (int j = 0; j < K; ++j)
-#pragma unroll
-                        for (int k = 0; k < K; ++k) xi[j][k] += ah[i][j] * th[j][k] * v[k];
-                }
-#pragma unroll
-                for (int j = 0; j < K; ++j) {
-                    double s = 0.0;
-#pragma unroll
-                    for (int k = 0; k < K; ++k) s += th[j][k] * v[k];
-                    beta[j] = s;
-                    alpha[j] = ah[i][j];
-                }
-            }
-        }
+        double xi[K][K], logp;
+        bool done = false;
+        if (!__any(slot >= 0 && !(lx >= kDirectLog))) done = recursions<false>(th, xi, logp);
+        if (!done) (void)recursions<true>(th, xi, logp);
         wave_lds_sync();
 
         // 4. G = df/d log x on the entry lanes
@@ -601,65 +669,51 @@ struct HmmEval {
     }
 };
 
+// One wave a group: a chain's trees take their own time, and with four chains
+// a group the group's LDS and registers stayed taken until the longest was
+// done (8,192 chains of 600 steps, depth 6: 5.64 ms; two a group 4.76, one
+// 4.54).  Two waves a SIMD: the recursions' and the tree's state take 256
+// registers, the occupancies most of 16 KB of LDS.  With the prefix and the
+// suffix both as matrix products over the lanes, every product rescaled and
+// every step normalised, the four-chain form took 6.92 ms.  What bounds it is the chain
+// of dependent fp64 instructions and LDS shuffles of one evaluation.
 template <int K, bool EXT>
-__global__ void __launch_bounds__(kHmmChainsPerGroup * kWave, 2) sampler_hmm_kernel(SamplerArgs A, HmmView hv,
-                                                                                     int cpg)
+__global__ void __launch_bounds__(kWave, 2) sampler_hmm_kernel(SamplerArgs A, HmmView hv)
 {
     extern __shared__ double lds[];
-    const int wave = threadIdx.x / kWave;
-    const int64_t chain = (int64_t)blockIdx.x * cpg + wave;
-    if (wave >= cpg || chain >= A.num_chains) return;
+    const int64_t chain = blockIdx.x;
     const HmmLds L = hmm_lds(K, hv.V, hv.T, hv.Tsup, A.data.D, A.max_depth, EXT ? A.sub_merge : 0);
-    double* base = lds + (int64_t)wave * L.wave;
     HmmEval<K> ev;
-    ev.init_chain(hv, A.data.D, base + L.gam_off, base + L.phi_off, base + L.row_off);
-    run_chain<1, EXT>(A, ev, chain, base + L.s_off);
+    ev.init_chain(hv, A.data.D, lds + L.gam_off, lds + L.phi_off, lds + L.row_off);
+    run_chain<1, EXT>(A, ev, chain, lds + L.s_off);
 }
 
 template <int K>
-__global__ void __launch_bounds__(kHmmChainsPerGroup * kWave, 2) hmm_potential_kernel(HmmView hv, int D,
-                                                                                       const double* Q, int64_t n,
-                                                                                       double* out_U,
-                                                                                       double* out_grad, int cpg)
+__global__ void __launch_bounds__(kWave, 2) hmm_potential_kernel(HmmView hv, int D, const double* Q, double* out_U,
+                                                                 double* out_grad)
 {
     extern __shared__ double lds[];
-    const int wave = threadIdx.x / kWave;
-    const int64_t p = (int64_t)blockIdx.x * cpg + wave;
-    if (wave >= cpg || p >= n) return;
+    const int64_t p = blockIdx.x;
     const int l = lane();
     const HmmLds L = hmm_lds(K, hv.V, hv.T, hv.Tsup, D, 1, 0);
-    double* base = lds + (int64_t)wave * L.wave;
     HmmEval<K> ev;
-    ev.init_chain(hv, D, base + L.gam_off, base + L.phi_off, base + L.row_off);
+    ev.init_chain(hv, D, lds + L.gam_off, lds + L.phi_off, lds + L.row_off);
     double q[1] = {l < D ? Q[p * D + l] : 0.0}, U, g[1];
     ev.eval(q, U, g);
     if (l < D) out_grad[p * D + l] = g[0];
     if (l == 0) out_U[p] = U;
 }
 
-// Chains (waves) per group whose LDS fits, from 4 down to 1; 0 if none.
-inline int hmm_chains_per_group(const HmmLds& L, int64_t n)
-{
-    for (int cpg = kHmmChainsPerGroup; cpg >= 1; cpg /= 2) {
-        if (cpg > n && cpg > 1) continue;
-        if ((size_t)cpg * L.wave * sizeof(double) <= sampler::kMaxGroupLds) return cpg;
-    }
-    return 0;
-}
-
 template <int K, bool EXT>
 hipError_t hmm_sampler_launch(const SamplerArgs& a, const HmmView& hv, hipStream_t stream)
 {
     const HmmLds L = hmm_lds(K, hv.V, hv.T, hv.Tsup, a.data.D, a.max_depth, a.sub_merge);
-    const int cpg = hmm_chains_per_group(L, a.num_chains);
-    if (cpg == 0) return hipErrorInvalidValue;
-    const size_t lds = (size_t)cpg * L.wave * sizeof(double);
+    const size_t lds = (size_t)L.wave * sizeof(double);
+    if (lds > sampler::kMaxGroupLds) return hipErrorInvalidValue;
     const void* k = (const void*)sampler_hmm_kernel<K, EXT>;
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    const unsigned grid = (unsigned)((a.num_chains + cpg - 1) / cpg);
-    hipLaunchKernelGGL((sampler_hmm_kernel<K, EXT>), dim3(grid), dim3(kHmmChainsPerGroup * kWave), lds, stream, a,
-                       hv, cpg);
+    hipLaunchKernelGGL((sampler_hmm_kernel<K, EXT>), dim3((unsigned)a.num_chains), dim3(kWave), lds, stream, a, hv);
     return hipGetLastError();
 }
 

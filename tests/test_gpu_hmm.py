@@ -96,6 +96,35 @@ def _adapt_bar(orc, hm, ref, **kw):
     return max(1e-9, 100.0 * s)
 
 
+# Both forms of the recursions: rows whose smallest entry lies on either side
+# of e^-30, and sequences whose lanes (8 steps each) favour one state in turn,
+# so that a product over lanes loses e^-20 (2^-29) or e^-29 (2^-42) a lane and
+# leaves the direct form's range; a lane without steps, a first step without
+# transition, positions that are not numbers.  Bars as above, up to e^-200, of
+# which three still multiply within fp64's range (e^-708): a rescaled product of
+# matrices, in either form, holds no wider ratio between its entries.
+@pytest.mark.parametrize("K,V", [(2, 2), (3, 3), (4, 5)])
+@pytest.mark.parametrize("T,Tsup", [(512, 0), (505, 1), (100, 40)])
+def test_potential_direct_and_careful(sampler, orc, K, V, T, Tsup):
+    w = ((np.arange(T) // 8) % 2).astype(np.uint8)
+    w[::37] = V - 1
+    z = (np.arange(max(Tsup, 1)) % K).astype(np.uint8)[:Tsup]
+    Q = []
+    for a in (1.0, 10.0, 20.0, 29.0, 29.9, 30.0, 30.1, 45.0, 200.0):
+        theta = np.full((K, K), -a)
+        theta[np.arange(K), np.arange(K)] = 0.0
+        phi = np.full((K, V), -a)
+        phi[np.arange(K), np.arange(K) % V] = 0.0
+        # free logits: relative to the row's last entry
+        Q.append(np.concatenate([(theta[:, :-1] - theta[:, -1:]).ravel(), (phi[:, :-1] - phi[:, -1:]).ravel()]))
+    Q = np.array(Q)
+    say("hmm direct and careful", K, V, T, Tsup)
+    _check_potential(sampler, orc, w, z, K, V, Q)
+    Q[0, 0] = np.nan
+    U, _ = sampler.hmm_potential_grad(w, z, K, V, Q[:1])
+    assert np.isnan(U[0])
+
+
 @pytest.mark.parametrize("adapt", [False, True])
 def test_sampler_matches_oracle(sampler, orc, adapt):
     w, z = _seq(600, 100, 3, 10, key=6)
