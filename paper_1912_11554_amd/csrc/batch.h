@@ -111,6 +111,21 @@ __device__ __forceinline__ v4f mfma(v8bf a, v8bf b, v4f c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// A sum of corrections, held to the finite range.  Where a factor is infinite
+// or a product leaves the fp32 range, the leading products x1 q1 (256 times
+// the corrections) hold the infinity or NaN the fp32 product has, and the
+// corrections hold inf - inf and inf * 0 on top of it: a NaN becomes
+// -FLT_MAX here, which no infinity and no NaN notices.  One instruction a sum
+// (the bound and its negation are one scalar register).
+__device__ __forceinline__ v4f finite(v4f c)
+{
+    float big;
+    asm("s_mov_b32 %0, 0x7f7fffff" : "=s"(big));
+#pragma unroll
+    for (int r = 0; r < 4; ++r) c[r] = __builtin_amdgcn_fmed3f(c[r], -big, big);
+    return c;
+}
+
 // Negative log-likelihood and residual of one (row, position) from eta in
 // fp32, with sgn = 1 - 2y: t = sgn eta, loss = softplus(t) = max(t, 0) +
 // ln 2 log2(1 + e), residual = sgn sigmoid(t), e = exp(-|t|); three
@@ -247,8 +262,8 @@ __device__ __forceinline__ void columns(const char* xs, const WaveQ& Q, int tp, 
             c0 = mfma(z0, Q.q[0][t], c0);
             c1 = mfma(z1, Q.q[0][t], c1);
         }
-        e0 += c0;
-        e1 += c1;
+        e0 += finite(c0);
+        e1 += finite(c1);
     }
     if (tail) {  // uniform
         const char* x = xs + G::kTailAt + (tp * kTileRows + 4 * jj) * (kTail * 4);
@@ -327,7 +342,7 @@ __device__ __forceinline__ void compute_stage(const char* xs, const WaveQ& Q, Wa
                 c = mfma(x[0], R[2], c);
                 c = mfma(x[1], R[1], c);
                 c = mfma(x[2], R[0], c);
-                acc.g[mt] += c;
+                acc.g[mt] += finite(c);
             }
             __builtin_amdgcn_s_setprio(0);
         }

@@ -77,6 +77,40 @@ def test_batched_potential_full_size_samples(sampler, orc):
     np.testing.assert_allclose(U, U2, rtol=1e-6)
 
 
+# an infinite feature in the matrix columns: its row's loss is infinite or
+# zero and its column's sum infinite or (infinity times a residual of zero)
+# NaN, as in fp32 products; every other column of a position is unharmed
+# (w_2 has bits in one bf16 part only, and in all three)
+@pytest.mark.parametrize("N,D", [(128, 20), (192, 129)])
+def test_batched_infinite_feature(sampler, N, D):
+    X, y, _ = _data(N, D, [72, D])
+    X[5, 2] = np.inf
+    y[5] = 0
+    W = np.random.default_rng(D).normal(0.0, 0.1, size=(4, D)).astype(np.float32).astype(np.float64)
+    W[:, 2] = [0.5, -0.5, 0.1, -0.1]
+    up = W[:, 2] > 0
+    say("infinite feature", N, D)
+    d = sampler.data(X, y)
+    U, G = d.potential_grad(W, batched=True)
+    ll, elpd, _ = d.log_likelihood(W)
+    Y = d.posterior_predictive(W, seed=3)
+    assert np.array_equal(Y[:, 5], up)
+    assert np.all(U[up] == np.inf) and np.all(ll[up] == -np.inf)
+    assert np.all(G[up, 2] == np.inf) and np.all(np.isnan(G[~up, 2]))
+    X64 = X.astype(np.float64)
+    sgn = 1.0 - 2.0 * y
+    t = sgn[None, :] * (W @ X64.T)
+    ref = np.logaddexp(0.0, t).sum(axis=1)
+    np.testing.assert_allclose(ll[~up], -ref[~up], rtol=1e-5)
+    np.testing.assert_allclose(elpd, np.logaddexp.reduce(-ref) - np.log(4.0), rtol=1e-5)
+    X64[5, 2] = 0.0
+    g = (sgn / (1.0 + np.exp(-t))) @ X64 + W
+    others = np.arange(D) != 2
+    tol = np.array([grad_tol(X64, W[k], g[k], 1.0, 1e-5) for k in range(4)])
+    assert np.all(np.abs(G - g)[:, others] <= tol[:, others])
+    d.free()
+
+
 def test_batched_potential_rejects(sampler):
     import paper_1912_11554_amd as nuts
     X, y, _ = _data(100, 133, [71, 1])
