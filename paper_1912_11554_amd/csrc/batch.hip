@@ -118,10 +118,6 @@ namespace {
 using batch::WaveAcc;
 using batch::WaveQ;
 
-// Store a wave's partial row for its 16 positions: G columns from the
-// matrix-core accumulators, the tail columns and the loss from the lanes of
-// the first row group.  ATOMIC selects agent-scope stores (read by other
-// groups of the same launch).
 // Buffer resource word 3 for raw dword access on gfx9-family devices, and the
 // cache-policy operand of a buffer access at agent scope (the sc1 bit: the
 // access is coherent across the device's L2 caches, as an agent-scope atomic
@@ -130,9 +126,21 @@ using batch::WaveQ;
 constexpr int kBufferWord3 = 0x00020000;
 constexpr int kCachePolicyAgent = 16;
 
+// The resource of a buffer that starts at `base`, the same address in every
+// lane of the wave; what differs from lane to lane belongs into the access's
+// 32-bit offset.  (From a base that differed from lane to lane, one of a
+// wave's 16 positions, the compiler made a loop over the distinct bases, and
+// where registers were short, at 101 to 128 columns, that loop reloaded the
+// resource's upper words from scratch memory over the base it still needed:
+// from the second base on the lanes read and wrote memory that was not
+// theirs.)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, 0x7fffffff, kBufferWord3);
+    const uint64_t b = reinterpret_cast<uint64_t>(base);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((uint64_t)hi << 32 | lo), (short)0, 0x7fffffff,
+                                             kBufferWord3);
 }
 
 template <bool ATOMIC>
@@ -147,6 +155,10 @@ __device__ __forceinline__ void put_d(double* p, double v)
     if constexpr (ATOMIC) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else *p = v;
 }
+// Store a wave's partial rows for its 16 positions into the group's P and L: G
+// columns from the matrix-core accumulators, the tail columns and the loss
+// from the lanes of the first row group.  ATOMIC selects agent-scope stores
+// (read by other groups of the same launch).
 template <int KT, bool ATOMIC>
 __device__ __forceinline__ void store_partials(const BatchView& bv, WaveAcc& acc, int widx, int pw, float* P,
                                                double* L)
@@ -157,11 +169,12 @@ __device__ __forceinline__ void store_partials(const BatchView& bv, WaveAcc& acc
     batch::reduce_position(acc);
     const int slot = widx * 16 + m;
     float* row = P + (int64_t)slot * pw;
+    const __amdgpu_buffer_rsrc_t rows = buffer_of(P);
 #pragma unroll
     for (int mt = 0; mt < KT; ++mt) {
         // 16-byte aligned: pw and 4 jj are multiples of 4
         if constexpr (ATOMIC)
-            __builtin_amdgcn_raw_buffer_store_b128(acc.g[mt], buffer_of(row), (16 * mt + 4 * jj) * 4, 0,
+            __builtin_amdgcn_raw_buffer_store_b128(acc.g[mt], rows, (slot * pw + 16 * mt + 4 * jj) * 4, 0,
                                                    kCachePolicyAgent);
         else
             *reinterpret_cast<batch::v4f*>(row + 16 * mt + 4 * jj) = acc.g[mt];
@@ -526,18 +539,20 @@ struct PassBf16 {
     {
         __hip_atomic_store(dst + col, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // in 16-byte agent-scope loads: this lane's columns of every K-step (none
-    // past the matrix columns), then the tail
-    __device__ static void get(const float* src, Q& q)
+    // row `slot` of the tile's positions, in 16-byte agent-scope loads: this
+    // lane's columns of every K-step (none past the matrix columns), then the
+    // tail
+    __device__ static void get(const float* tile, int slot, Q& q)
     {
         const int jj = lane() >> 4;
-        const __amdgpu_buffer_rsrc_t qr = buffer_of(src);
+        const __amdgpu_buffer_rsrc_t qr = buffer_of(tile);
+        const int at = slot * kBatchQWidth;
 #pragma unroll
         for (int t = 0; t < batch::Geo<KT>::kSteps; ++t) {
             float v[8];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const batch::v4f f = __builtin_amdgcn_raw_buffer_load_b128(qr, (32 * t + 8 * jj + 4 * h) * 4, 0,
+                const batch::v4f f = __builtin_amdgcn_raw_buffer_load_b128(qr, (at + 32 * t + 8 * jj + 4 * h) * 4, 0,
                                                                            kCachePolicyAgent);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[4 * h + i] = 32 * t + 8 * jj + 4 * h + i < 16 * KT ? f[i] : 0.0f;
@@ -547,7 +562,7 @@ struct PassBf16 {
 #pragma unroll
             for (int p = 0; p < batch::kParts; ++p) q.q[p][t] = parts[p];
         }
-        const batch::v4f tv = __builtin_amdgcn_raw_buffer_load_b128(qr, 16 * KT * 4, 0, kCachePolicyAgent);
+        const batch::v4f tv = __builtin_amdgcn_raw_buffer_load_b128(qr, (at + 16 * KT) * 4, 0, kCachePolicyAgent);
 #pragma unroll
         for (int k = 0; k < batch::kTail; ++k) q.qt[k] = tv[k];
     }
@@ -580,18 +595,19 @@ struct PassF32 {
         if (col >= 16 * KT && col < 16 * KT + batch::kTail)
             __hip_atomic_store(dst + 16 * KP + (col - 16 * KT), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __device__ static void get(const float* src, Q& q)
+    __device__ static void get(const float* tile, int slot, Q& q)
     {
         const int jj = lane() >> 4;
-        const __amdgpu_buffer_rsrc_t qr = buffer_of(src);
+        const __amdgpu_buffer_rsrc_t qr = buffer_of(tile);
+        const int at = slot * kBatchQWidth;
 #pragma unroll
         for (int t = 0; t < KP; ++t) {
-            const batch::v4f v = __builtin_amdgcn_raw_buffer_load_b128(qr, (jj * 4 * KP + 4 * t) * 4, 0,
+            const batch::v4f v = __builtin_amdgcn_raw_buffer_load_b128(qr, (at + jj * 4 * KP + 4 * t) * 4, 0,
                                                                        kCachePolicyAgent);
 #pragma unroll
             for (int i = 0; i < 4; ++i) q.q[4 * t + i] = v[i];
         }
-        const batch::v4f tv = __builtin_amdgcn_raw_buffer_load_b128(qr, 16 * KP * 4, 0, kCachePolicyAgent);
+        const batch::v4f tv = __builtin_amdgcn_raw_buffer_load_b128(qr, (at + 16 * KP) * 4, 0, kCachePolicyAgent);
 #pragma unroll
         for (int k = 0; k < batch::kTail; ++k) q.qt[k] = tv[k];
     }
@@ -739,11 +755,8 @@ __device__ int batch_collective(const BatchCtx& c, BatchShared<SamplerPass<KT, E
         Pass::template loop<false>(c.bv, c.h0, c.h1, 0, sh.xs, Q, acc);
     } else {
         const int widx = wave - 1;
-        const int m = l & 15;
-        const float* qsrc = c.qbuf + ((int64_t)par * c.tiles * kBatchTileChains +
-                                      (int64_t)c.t * kBatchTileChains + widx * 16 + m) * kBatchQWidth;
         typename Pass::Q Q;
-        Pass::get(qsrc, Q);
+        Pass::get(c.qbuf + ((int64_t)par * c.tiles + c.t) * kBatchTileChains * kBatchQWidth, widx * 16 + (l & 15), Q);
         WaveAcc acc;
         batch::zero(acc);
         Pass::template loop<true>(c.bv, c.h0, c.h1, (int)threadIdx.x - kWave, sh.xs, Q, acc);
@@ -774,8 +787,7 @@ __device__ int batch_collective(const BatchCtx& c, BatchShared<SamplerPass<KT, E
         // first group and is not added.  (4-byte loads of the same rows took three
         // times as long: the gather is bound by the count of uncached
         // requests, not by bytes.)
-        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float*>(src), (short)0, 0x7fffffff, kBufferWord3);
+        const __amdgpu_buffer_rsrc_t rsrc = buffer_of(src);
         const int nl = (c.bv.D + 3) / 4;
         const int lc = l < nl ? l : nl - 1;
         double s4[4] = {0.0, 0.0, 0.0, 0.0};

@@ -1,7 +1,10 @@
 // The batched contraction on the fp32 matrix-core instruction, for the sampler
 // kernels with the optional features.  (With the bf16 parts of batch.h those
 // kernels faulted the GPU in a run of 24 chains with merge-structured subtree
-// proposals on 500 x 129; the cause was not found, so they keep this form.)
+// proposals on 500 x 129: at 117 to 132 columns the loop the compiler then made
+// of a position load from a per-lane base overwrote that base, see buffer_of in
+// batch.hip.  The loads have one base a wave now; these kernels have not been
+// moved since.)
 //
 // Layout of a stage in memory: 64 rows of `stride32` floats; the first 16 kp of
 // a row (kp = kt rounded up to a multiple of 4) hold the matrix columns,

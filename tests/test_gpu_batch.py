@@ -140,6 +140,13 @@ def _compare_decisions(gpu, ref, c, atol):
     (100, 20, 130, 3, [0, 1, 64, 127, 128, 129]),     # two tiles, the second nearly empty
     (60, 9, 300, 3, [0, 255, 256, 299]),              # two launches (256 + 44 chains)
     (20000, 33, 16, 3, [0, 7, 15]),                   # many stages per group
+    # the registers are shortest from seven chunks on: first and last shape of
+    # seven and eight chunks
+    (500, 101, 24, 3, [0, 15, 16, 23]),
+    (500, 112, 24, 3, [0, 15, 16, 23]),
+    (500, 116, 24, 3, [0, 15, 16, 23]),
+    (500, 117, 24, 3, [0, 15, 16, 23]),
+    (500, 128, 24, 3, [0, 15, 16, 23]),
 ])
 def test_batch_sampler_matches_oracle(sampler, orc, N, D, C, iters, check):
     X, y, _ = _data(N, D, [72, N * 1000 + D])
