@@ -11,11 +11,13 @@
 // The products are fp32 products on the bf16 matrix cores (16 times the rate
 // of the fp32 ones).  Every fp32 factor is split into three bf16 parts, x = x1
 // + x2 + x3 with x1 = bf16(x), x2 = bf16(x - x1), x3 = bf16(x - x1 - x2): 8
-// bits each, so the three hold all 24 bits of x and the split is exact (short
-// of the subnormal range).  x q is then the sum of nine products of bf16
-// parts, each exact in fp32; the six of x1 q1, x1 q2, x2 q1, x1 q3, x2 q2 and
-// x3 q1 are taken, and the three left out are below 2^-25 |x q| together,
-// under half the rounding of one fp32 multiply-add.  The sums are the matrix
+// bits each, so the three hold all 24 bits of x and the split is exact for |x|
+// >= 2^-110 (x1 of values that would round to infinity is held to the largest
+// bf16 value); below that the bits of x under 2^-133 are not bf16 values, and
+// the sum of the parts is off by at most 2^-134.  x q is then the sum of nine
+// products of bf16 parts, each exact in fp32; the six of x1 q1, x1 q2, x2 q1,
+// x1 q3, x2 q2 and x3 q1 are taken, and the three left out are below 2^-25
+// |x q| together, under half the rounding of one fp32 multiply-add.  The sums are the matrix
 // cores' fp32 accumulations over 32 products at a time (the fp32 instruction
 // rounded after every four).  Against 64-bit arithmetic the gradient of 256
 // positions on 200,000 x 129 is off by 7.4e-7 (8.5e-7 with the fp32
@@ -83,21 +85,41 @@ struct Geo {
     static_assert(kBytes == batch_stage_bytes(KT), "the host sizes stages as the kernels read them");
 };
 
-// bf16 parts of n fp32 values, part by part.
+// bf16 parts of two fp32 values of at most the largest bf16 value, infinities or
+// NaN.
 __device__ __forceinline__ void split3(v2f x, v2bf& a, v2bf& b, v2bf& c)
 {
     a = __builtin_convertvector(x, v2bf);
     x -= __builtin_convertvector(a, v2f);  // exact
     b = __builtin_convertvector(x, v2bf);
     x -= __builtin_convertvector(b, v2f);  // exact
-    c = __builtin_convertvector(x, v2bf);  // exact
+    c = __builtin_convertvector(x, v2bf);  // exact above 2^-110
 }
+// The largest bf16 value.  A finite value that would round to infinity keeps it
+// as its first part (the rest has 16 bits, which the other two parts hold).
+constexpr float kBf16Max = 0x1.fep127f;
+__device__ __forceinline__ float first_part_range(float x)
+{
+    return fabsf(x) <= 0x1.fffffep127f ? __builtin_amdgcn_fmed3f(x, -kBf16Max, kBf16Max) : x;
+}
+// The same for any values.
+__device__ __forceinline__ void split3_any(v2f x, v2bf& a, v2bf& b, v2bf& c)
+{
+    a = __builtin_convertvector((v2f{first_part_range(x[0]), first_part_range(x[1])}), v2bf);
+    x -= __builtin_convertvector(a, v2f);  // exact
+    b = __builtin_convertvector(x, v2bf);
+    x -= __builtin_convertvector(b, v2f);  // exact
+    c = __builtin_convertvector(x, v2bf);  // exact above 2^-110
+}
+// ANY: split3_any, else split3.
+template <bool ANY>
 __device__ __forceinline__ void split3(const float (&x)[8], v8bf (&out)[kParts])
 {
 #pragma unroll
     for (int i = 0; i < 8; i += 2) {
         v2bf a, b, c;
-        split3(v2f{x[i], x[i + 1]}, a, b, c);
+        if constexpr (ANY) split3_any(v2f{x[i], x[i + 1]}, a, b, c);
+        else split3(v2f{x[i], x[i + 1]}, a, b, c);
         out[0][i] = a[0];
         out[0][i + 1] = a[1];
         out[1][i] = b[0];
@@ -156,6 +178,28 @@ struct WaveQ {
     v8bf q[kParts][kBatchMaxKT / 2];
     float qt[kTail];
 };
+
+// Q's parts from the columns v[t][i] of every K-step.  A wave with a value above
+// the largest bf16 value takes a form of its own (one uniform branch: 256
+// chains on 200,000 x 129 8,297 us; 8,672 with every value held to the range).
+template <int STEPS>
+__device__ __forceinline__ void split_positions(const float (&v)[STEPS > 0 ? STEPS : 1][8], WaveQ& Q)
+{
+    float top = 0.0f;
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) top = __builtin_fmaxf(top, fabsf(v[t][i]));
+    const bool any = __any(top > kBf16Max);
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t) {
+        v8bf parts[kParts];
+        if (any) split3<true>(v[t], parts);
+        else split3<false>(v[t], parts);
+#pragma unroll
+        for (int p = 0; p < kParts; ++p) Q.q[p][t] = parts[p];
+    }
+}
 
 struct WaveAcc {
     v4f g[kBatchMaxKT];  // G[16 mt + 4 (l / 16) + r][l % 16] in g[mt][r]
@@ -316,7 +360,7 @@ __device__ __forceinline__ void compute_stage(const char* xs, const WaveQ& Q, Wa
         acc.loss += (double)lsum;
         if constexpr (KT > 0) {
             v8bf R[kParts];
-            split3(res, R);
+            split3<false>(res, R);
             // lane i of a 16-lane group reads columns 4 (i % 4) .. + 3 of row
             // 4 jj + i / 4 of a 16-column chunk
             const int i = l & 15;

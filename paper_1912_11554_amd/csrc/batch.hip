@@ -36,7 +36,7 @@ __global__ void __launch_bounds__(256) to_batch_kernel(const float* __restrict__
 #pragma unroll
             for (int k = 0; k < 8; ++k) v[k] = 8 * slot + k < 16 * KT ? value(8 * slot + k) : 0.0f;
             batch::v8bf parts[batch::kParts];
-            batch::split3(v, parts);
+            batch::split3<true>(v, parts);
             char* dst = img + row * G::kRow + (slot ^ batch::swizzle<KT>(row & (batch::kTileRows - 1))) * 16;
 #pragma unroll
             for (int q = 0; q < batch::kParts; ++q)
@@ -194,19 +194,16 @@ __device__ __forceinline__ void load_q(const BatchView& bv, const double* __rest
 {
     const int jj = lane() >> 4;
     const double* w = W + pos * bv.D;
+    constexpr int kSteps = batch::Geo<KT>::kSteps;
+    float v[kSteps > 0 ? kSteps : 1][8];
 #pragma unroll
-    for (int t = 0; t < batch::Geo<KT>::kSteps; ++t) {
-        float v[8];
+    for (int t = 0; t < kSteps; ++t)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int col = 32 * t + 8 * jj + i;
-            v[i] = (live && col < 16 * KT && col < bv.D) ? (float)w[col] : 0.0f;
+            v[t][i] = (live && col < 16 * KT && col < bv.D) ? (float)w[col] : 0.0f;
         }
-        batch::v8bf parts[batch::kParts];
-        batch::split3(v, parts);
-#pragma unroll
-        for (int q = 0; q < batch::kParts; ++q) Q.q[q][t] = parts[q];
-    }
+    batch::split_positions<kSteps>(v, Q);
 #pragma unroll
     for (int k = 0; k < batch::kTail; ++k) Q.qt[k] = (live && k < bv.tc) ? (float)w[16 * KT + k] : 0.0f;
 }
@@ -547,21 +544,19 @@ struct PassBf16 {
         const int jj = lane() >> 4;
         const __amdgpu_buffer_rsrc_t qr = buffer_of(tile);
         const int at = slot * kBatchQWidth;
+        constexpr int kSteps = batch::Geo<KT>::kSteps;
+        float v[kSteps > 0 ? kSteps : 1][8];
 #pragma unroll
-        for (int t = 0; t < batch::Geo<KT>::kSteps; ++t) {
-            float v[8];
+        for (int t = 0; t < kSteps; ++t) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const batch::v4f f = __builtin_amdgcn_raw_buffer_load_b128(qr, (at + 32 * t + 8 * jj + 4 * h) * 4, 0,
                                                                            kCachePolicyAgent);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[4 * h + i] = 32 * t + 8 * jj + 4 * h + i < 16 * KT ? f[i] : 0.0f;
+                for (int i = 0; i < 4; ++i) v[t][4 * h + i] = 32 * t + 8 * jj + 4 * h + i < 16 * KT ? f[i] : 0.0f;
             }
-            batch::v8bf parts[batch::kParts];
-            batch::split3(v, parts);
-#pragma unroll
-            for (int p = 0; p < batch::kParts; ++p) q.q[p][t] = parts[p];
         }
+        batch::split_positions<kSteps>(v, q);
         const batch::v4f tv = __builtin_amdgcn_raw_buffer_load_b128(qr, (at + 16 * KT) * 4, 0, kCachePolicyAgent);
 #pragma unroll
         for (int k = 0; k < batch::kTail; ++k) q.qt[k] = tv[k];

@@ -111,6 +111,46 @@ def test_batched_infinite_feature(sampler, N, D):
     d.free()
 
 
+# finite features and weights at the ends of the fp32 range: the largest value
+# against weights that leave it in range (zero among them), and the reverse.  A
+# factor below 2^-110 is off by at most 2^-134 in its bf16 parts, which adds
+# 2^-134 times the other factor to a row's eta.
+@pytest.mark.parametrize("N,D", [(128, 20), (192, 129)])
+@pytest.mark.parametrize("big", ["feature", "weight"])
+def test_batched_ends_of_the_range(sampler, N, D, big):
+    X, y, _ = _data(N, D, [74, D])
+    top = np.float32(np.finfo(np.float32).max)
+    W = np.random.default_rng(D).normal(0.0, 0.1, size=(6, D)).astype(np.float32).astype(np.float64)
+    small = np.array([0.0, 2.0**-126, 3e-38, -1.1e-37, 0.5, -1.0], dtype=np.float32).astype(np.float64)
+    if big == "feature":
+        X[:, 2] = 0.0
+        X[5, 2], y[5] = top, 0
+        X[70, 2], y[70] = -top * np.float32(0.9975), 0
+        W[:, 2] = small
+    else:
+        X[:, 2] = small[np.arange(N) % 4]
+        W[:, 2] = [top, -top, top * np.float32(0.9985), -top * np.float32(0.5), 1.0, 0.0]
+    say("ends of the range", N, D, big)
+    d = sampler.data(X, y)
+    U, G = d.potential_grad(W, batched=True)
+    ll, _, pred = d.log_likelihood(W, pred_mean=True)
+    d.free()
+    X64 = X.astype(np.float64)
+    sgn = 1.0 - 2.0 * y
+    eta = W @ X64.T
+    t = sgn[None, :] * eta
+    ref = np.logaddexp(0.0, t).sum(axis=1)
+    off = 2.0**-134 * (np.abs(W).sum(axis=1)[:, None] + np.abs(X64).sum(axis=1)[None, :])
+    assert np.all(np.abs(ll + ref) <= 1e-5 * ref + off.sum(axis=1))
+    sig = 0.5 * (1.0 + np.tanh(0.5 * eta))
+    assert np.all(np.abs(pred - sig.mean(axis=0)) <= 1e-5 + 0.25 * off.mean(axis=0))
+    g = (sgn * 0.5 * (1.0 + np.tanh(0.5 * t))) @ X64
+    prior = 0.5 * (W**2).sum(axis=1) + 0.5 * D * np.log(2.0 * np.pi)
+    assert np.all(np.abs(U - (ref + prior)) <= 1e-5 * (ref + prior) + off.sum(axis=1))
+    tol = 1e-5 * (np.abs(g + W) + np.abs(X64).sum(axis=0) + np.abs(W)) + 0.25 * off @ np.abs(X64)
+    assert np.all(np.abs(G - (g + W)) <= tol + 1e-5 * (np.arange(D) != 2))
+
+
 def test_batched_potential_rejects(sampler):
     import paper_1912_11554_amd as nuts
     X, y, _ = _data(100, 133, [71, 1])
