@@ -934,7 +934,10 @@ int nuts_sample_data(nuts_handle* h, const nuts_data* d, uint32_t flags, double 
 
     DeviceScope ds(h->device);
     int path = o.path;
-    if (per_chain && (path == NUTS_PATH_GRID || path == NUTS_PATH_BATCH))
+    // (AUTO runs chains with data of their own on the grid path too, where the
+    // wave path takes them as well: D <= 64)
+    if (per_chain && (path == NUTS_PATH_GRID || path == NUTS_PATH_BATCH ||
+                      (path == NUTS_PATH_AUTO && !wave_path_supports(d->view))))
         return fail(h, NUTS_EUNSUPPORTED, "the grid and batch paths run chains on shared data only");
     GridPlan grid_plan{0, 0, 0};
     if (path == NUTS_PATH_AUTO) {

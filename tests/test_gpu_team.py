@@ -57,6 +57,18 @@ def test_chains_with_their_own_data(sampler, orc, C, N, D):
     _check(orc, X, y, r, sorted({0, 1, C // 2, C - 2, C - 1}), 22, per_chain=True, **kw)
 
 
+def test_wide_data_of_their_own_is_refused(sampler):
+    import paper_1912_11554_amd as nuts
+    sets = [workloads.make_logistic(20, 65, w_scale=0.1, key=[75, c]) for c in range(3)]
+    X, y = np.stack([s[0] for s in sets]), np.stack([s[1] for s in sets])
+    say("wide per-chain data")
+    for path in (nuts.NUTS_PATH_AUTO, nuts.NUTS_PATH_WAVE, nuts.NUTS_PATH_GRID, nuts.NUTS_PATH_BATCH):
+        with pytest.raises(nuts.NutsError) as e:
+            sampler.sample(X, y, step_size=0.1, num_chains=3, num_warmup=0, num_samples=1, max_tree_depth=2,
+                           per_chain=True, path=path)
+        assert e.value.code == nuts.NUTS_EUNSUPPORTED
+
+
 # launches of fewer chains than the call has: shared rows that need several
 # groups a chain; and wide rows, which stream, side by side
 @pytest.mark.parametrize("C,N,D", [(12, 20000, 25), (150, 3000, 10), (9, 1500, 100)])
