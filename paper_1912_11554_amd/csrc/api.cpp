@@ -22,10 +22,11 @@ struct nuts_data {
     DataView view;
     void* X = nullptr;
     uint8_t* y = nullptr;
-    // row-stage copy for the batched (matrix-core) path, built on first use
+    // row-stage copies for the batched (matrix-core) path, each built on first
+    // use: bf16 parts, and fp32 for the sampler kernels with the optional
+    // features
     BatchView batch{};
     void* bX = nullptr;
-    // its fp32 form for the sampler kernels with the optional features
     float* bX32 = nullptr;
     uint8_t* by32 = nullptr;
 };
@@ -664,11 +665,12 @@ int nuts_data_potential_grad_noalloc(nuts_handle* h, const nuts_data* d, double 
     return NUTS_OK;
 }
 
-// The row-stage layout of a shared fp32 data set (built on first use).
-static int ensure_batch_layout(nuts_handle* h, const nuts_data* dc)
+// The row-stage layouts of a shared fp32 data set: the shape, the stages of bf16
+// parts, the fp32 stages (the last two each built on first use).  Where the
+// device has no room for one, the error is the call's alone: AUTO goes on with
+// another path.
+static int batch_layout_shape(nuts_handle* h, nuts_data* d)
 {
-    nuts_data* d = const_cast<nuts_data*>(dc);
-    if (d->bX) return NUTS_OK;
     if (d->view.dtype != NUTS_F32)
         return fail(h, NUTS_EUNSUPPORTED, "the batched path takes fp32 data");
     if (d->view.nds != 1) return fail(h, NUTS_EUNSUPPORTED, "the batched path takes one shared data set");
@@ -676,39 +678,49 @@ static int ensure_batch_layout(nuts_handle* h, const nuts_data* dc)
     if (!batch_shape(d->view.D, &kt, &tc))
         return fail(h, NUTS_EUNSUPPORTED, "the batched path takes D <= %d (got %d)", 16 * kBatchMaxKT + 4,
                     d->view.D);
-    BatchView b{};
+    BatchView& b = d->batch;
     b.N = d->view.N;
     b.D = d->view.D;
     b.kt = kt;
     b.tc = tc;
     b.ns = (b.N + kBatchStageRows - 1) / kBatchStageRows;
-    const size_t xb = (size_t)b.ns * batch_stage_bytes(kt);
+    b.stride32 = batch_stride32(kt);
+    return NUTS_OK;
+}
+
+static int ensure_batch_layout(nuts_handle* h, const nuts_data* dc)
+{
+    nuts_data* d = const_cast<nuts_data*>(dc);
+    if (d->bX) return NUTS_OK;
+    const int rc = batch_layout_shape(h, d);
+    if (rc != NUTS_OK) return rc;
+    BatchView& b = d->batch;
+    const size_t xb = (size_t)b.ns * batch_stage_bytes(b.kt);
+    if (xb == 0) return NUTS_OK;
     void* X = nullptr;
-    if (xb) {
-        hipError_t e = hipMalloc(&X, xb);
-        if (e == hipSuccess) e = launch_to_batch_layout(d->view, b, X, h->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-        if (e != hipSuccess) {
-            if (X) (void)hipFree(X);
-            return fail(h, e == hipErrorOutOfMemory ? NUTS_ENOMEM : NUTS_EDEVICE, "batched layout: %s",
-                        hipGetErrorString(e));
-        }
+    hipError_t e = hipMalloc(&X, xb);
+    if (e == hipSuccess) e = launch_to_batch_layout(d->view, b, X, h->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        if (X) (void)hipFree(X);
+        return fail(h, e == hipErrorOutOfMemory ? NUTS_ENOMEM : NUTS_EDEVICE, "batched layout: %s",
+                    hipGetErrorString(e));
     }
     b.X = X;
-    d->batch = b;
     d->bX = X;
     return NUTS_OK;
 }
 
-// The fp32 layout of a data set that has the row-stage layout (built on first
-// use).
 static int ensure_batch_layout_f32(nuts_handle* h, const nuts_data* dc)
 {
     nuts_data* d = const_cast<nuts_data*>(dc);
     if (d->bX32) return NUTS_OK;
+    const int rc = batch_layout_shape(h, d);
+    if (rc != NUTS_OK) return rc;
     BatchView& b = d->batch;
-    b.stride32 = batch_stride32(b.kt);
     const size_t rows = (size_t)b.ns * kBatchStageRows;
+    if (rows == 0) return NUTS_OK;
     float* X = nullptr;
     uint8_t* y = nullptr;
     hipError_t e = hipMalloc(&X, rows * b.stride32 * sizeof(float));
@@ -716,6 +728,7 @@ static int ensure_batch_layout_f32(nuts_handle* h, const nuts_data* dc)
     if (e == hipSuccess) e = launch_to_batch_layout_f32(d->view, b, X, y, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) {
+        (void)hipGetLastError();
         if (X) (void)hipFree(X);
         if (y) (void)hipFree(y);
         return fail(h, e == hipErrorOutOfMemory ? NUTS_ENOMEM : NUTS_EDEVICE, "batched layout: %s", hipGetErrorString(e));
@@ -725,6 +738,12 @@ static int ensure_batch_layout_f32(nuts_handle* h, const nuts_data* dc)
     d->bX32 = X;
     d->by32 = y;
     return NUTS_OK;
+}
+
+// The layout that the sampler's kernel reads.
+static int ensure_sampler_layout(nuts_handle* h, const nuts_data* d, bool extended)
+{
+    return extended ? ensure_batch_layout_f32(h, d) : ensure_batch_layout(h, d);
 }
 
 int nuts_data_potential_grad_batched(nuts_handle* h, const nuts_data* d, double prior_scale, const double* W,
@@ -939,6 +958,16 @@ int nuts_sample_data(nuts_handle* h, const nuts_data* d, uint32_t flags, double 
     if (per_chain && (path == NUTS_PATH_GRID || path == NUTS_PATH_BATCH ||
                       (path == NUTS_PATH_AUTO && !wave_path_supports(d->view))))
         return fail(h, NUTS_EUNSUPPORTED, "the grid and batch paths run chains on shared data only");
+    SamplerArgs probe;  // what the choice of a path depends on
+    std::memset(&probe, 0, sizeof probe);
+    probe.data = d->view;
+    probe.max_depth = max_tree_depth;
+    probe.num_chains = num_chains;
+    probe.num_warmup = num_warmup;
+    probe.adapt_step = (flags & NUTS_ADAPT_STEP_SIZE) ? 1 : 0;
+    probe.uturn_gen = (flags & NUTS_UTURN_GENERALIZED) ? 1 : 0;
+    probe.sub_merge = sub_merge;
+    const bool extended = sampler_extended(probe);
     GridPlan grid_plan{0, 0, 0};
     if (path == NUTS_PATH_AUTO) {
         // many chains on a large shared fp32 data set: the matrix-core batch;
@@ -948,14 +977,8 @@ int nuts_sample_data(nuts_handle* h, const nuts_data* d, uint32_t flags, double 
         int kt = 0, tc = 0;
         const bool batchable = !per_chain && d->view.dtype == NUTS_F32 && num_chains >= 16 &&
                                (double)d->view.N * d->view.D >= 262144.0 && batch_shape(d->view.D, &kt, &tc);
-        SamplerArgs probe;
-        std::memset(&probe, 0, sizeof probe);
-        probe.data = d->view;
-        probe.max_depth = max_tree_depth;
-        probe.num_chains = num_chains;
-        probe.sub_merge = sub_merge;
-        if (batchable && ensure_batch_layout(h, d) == NUTS_OK &&
-            batch_sampler_supported(d->batch, max_tree_depth, sub_merge, h->num_cu)) {
+        if (batchable && ensure_sampler_layout(h, d, extended) == NUTS_OK &&
+            batch_sampler_supported(d->batch, max_tree_depth, sub_merge, extended, h->num_cu)) {
             path = NUTS_PATH_BATCH;
         } else if (wave_path_supports(d->view)) {
             grid_plan = plan_grid_sampler(d->view, max_tree_depth, sub_merge, num_chains, h->num_cu);
@@ -970,9 +993,9 @@ int nuts_sample_data(nuts_handle* h, const nuts_data* d, uint32_t flags, double 
     if (path == NUTS_PATH_WAVE && !wave_path_supports(d->view))
         return fail(h, NUTS_EUNSUPPORTED, "the one-wave-per-chain path takes D <= 64 (got %d)", d->view.D);
     if (path == NUTS_PATH_BATCH) {
-        const int rc = ensure_batch_layout(h, d);
+        const int rc = ensure_sampler_layout(h, d, extended);
         if (rc != NUTS_OK) return rc;
-        if (!batch_sampler_supported(d->batch, max_tree_depth, sub_merge, h->num_cu))
+        if (!batch_sampler_supported(d->batch, max_tree_depth, sub_merge, extended, h->num_cu))
             return fail(h, NUTS_EUNSUPPORTED, "the batch path needs >= %d compute units and D <= 132",
                         kBatchTileChains);
     }
@@ -996,10 +1019,6 @@ int nuts_sample_data(nuts_handle* h, const nuts_data* d, uint32_t flags, double 
         HIP_TRY(h, launch_sampler_wave(a, s));
         if (kev) HIP_TRY(h, hipEventRecord(kev[1], s));
     } else if (path == NUTS_PATH_BATCH) {
-        if (sampler_extended(a)) {
-            rc = ensure_batch_layout_f32(h, d);
-            if (rc != NUTS_OK) return rc;
-        }
         // launches of up to kBatchMaxTiles tiles of 128 chains, the groups of
         // the device split evenly between the tiles of a launch
         const int max_tiles = std::min(kBatchMaxTiles, h->num_cu / kBatchTileChains);

@@ -969,13 +969,13 @@ size_t batch_sampler_lds(const SamplerArgs& a)
 
 }  // namespace
 
-bool batch_sampler_supported(const BatchView& bv, int max_depth, int sub_merge, int num_cu)
+bool batch_sampler_supported(const BatchView& bv, int max_depth, int sub_merge, bool extended, int num_cu)
 {
     if (bv.D > 64 * 3 || num_cu < kBatchTileChains) return false;
     int per_cu = 0;
     const size_t lds =
-        (size_t)chain_lds_doubles(bv.D, max_depth, sub_merge, batch_edge_nodes(bv.D, sub_merge != 0)) * sizeof(double);
-    const void* k = batch_kernel_for(bv, sub_merge != 0);
+        (size_t)chain_lds_doubles(bv.D, max_depth, sub_merge, batch_edge_nodes(bv.D, extended)) * sizeof(double);
+    const void* k = batch_kernel_for(bv, extended);
     if (!k) return false;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kGroupWaves * kWave, lds) != hipSuccess) return false;
     return per_cu >= 1;

@@ -206,8 +206,8 @@ struct BatchView {
     int kt;          // 16-column chunks on the matrix cores
     int tc;          // tail columns on the vector ALUs (0..4)
     int64_t ns;      // stages: ceil(N / 64)
-    // the fp32 layout of batch_f32.h, for the sampler kernels with the
-    // optional features; null until such a launch
+    // the fp32 layout of batch_f32.h, which the sampler kernels with the
+    // optional features read instead of X; each null until first needed
     const float* X32;
     const uint8_t* y32;
     int stride32;    // floats a row
@@ -291,7 +291,7 @@ struct BatchSync {
 hipError_t launch_sampler_batch(const SamplerArgs& a, const BatchView& bv, int tiles, int groups, float* qbuf,
                                 float* P, double* L, BatchSync* sync, hipStream_t stream,
                                 hipEvent_t at_launch = nullptr);
-bool batch_sampler_supported(const BatchView& bv, int max_depth, int sub_merge, int num_cu);
+bool batch_sampler_supported(const BatchView& bv, int max_depth, int sub_merge, bool extended, int num_cu);
 constexpr int kBatchQWidth = 192;
 
 // Per-dtype kernel entry points (sampler_f32.hip, sampler_f64.hip).

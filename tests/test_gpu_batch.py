@@ -238,6 +238,27 @@ def test_batch_sampler_full_size_ten_iterations(sampler, orc):
         _compare_decisions(r, rf, c, atol=1e-5)
 
 
+def test_batch_sampler_builds_one_layout(sampler):
+    # the kernels with the optional features read fp32 stages, the others the
+    # bf16 parts: a call builds the one it reads (fp32: 132 floats and a label a
+    # row; bf16 parts: 788 bytes), give or take what an allocation rounds up to
+    import torch
+    N, D = 100000, 129
+    X, y, _ = _data(N, D, [76, 1])
+    kw = dict(step_size=1e-3, max_tree_depth=2, num_warmup=1, num_samples=1, num_chains=16, seed=5, path=3)
+    say("batch sampler layouts")
+    for extra, row in [({}, 788), (dict(adapt_step_size=True), 529), (dict(subtree_merge=True), 529)]:
+        d = sampler.data(X, y)
+        d.sample(**kw, **extra)  # the handle's workspaces, the kernel's scratch memory
+        d.free()
+        d = sampler.data(X, y)
+        before = torch.cuda.mem_get_info(0)[0]
+        d.sample(**kw, **extra)
+        used = before - torch.cuda.mem_get_info(0)[0]
+        d.free()
+        assert abs(used - N * row) <= 6 << 20, (extra, used)
+
+
 def test_batch_sampler_auto_and_resume(sampler):
     # AUTO picks the batch path for many chains on large fp32 data; a run
     # split in two calls (final state, first_iter) equals one call
