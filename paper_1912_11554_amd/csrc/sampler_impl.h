@@ -702,7 +702,7 @@ struct DualAvg {
 // log of the density kept by one leapfrog step of size e from (cur.q, r):
 // H0 - H', or -inf when H' is not a number.
 template <int DPL, class Eval>
-__device__ double step_log_ratio(Eval& ev, const Node<DPL>& cur, const double (&r)[DPL], double e,
+__device__ __forceinline__ double step_log_ratio(Eval& ev, const Node<DPL>& cur, const double (&r)[DPL], double e,
                                  const double (&im)[DPL], double H0)
 {
     Node<DPL> z = cur;
@@ -727,7 +727,7 @@ __device__ double step_log_ratio(Eval& ev, const Node<DPL>& cur, const double (&
 // halve (it does not) until that flips; the momentum is drawn under
 // kTagStepSize at counter t.  Adds the gradient evaluations to *evals.
 template <int DPL, class Eval>
-__device__ double find_step_size(Eval& ev, const Node<DPL>& cur, double eps, const double (&im)[DPL],
+__device__ __forceinline__ double find_step_size(Eval& ev, const Node<DPL>& cur, double eps, const double (&im)[DPL],
                                  const bool (&act)[DPL], uint64_t seed, uint64_t chain, uint64_t t,
                                  unsigned long long* evals)
 {
@@ -806,8 +806,14 @@ __device__ __forceinline__ void leapfrog_drift(const double (&q)[DPL], const dou
 // EXT = false compiles the optional features out (warmup adaptation of the
 // step size, the generalised U-turn criterion): the kernels without them keep
 // their registers for the tree and the data pass.
+//
+// Everything that takes the evaluator by reference is inlined by force: one
+// call that is not (the compiler stops at large bodies, the HMM's first) puts
+// the evaluator into scratch memory for the whole chain, and every evaluation
+// then reads its state from there (HMM with two states, adapted step size, one
+// chain: 10.6 us an evaluation; inlined 7.1).
 template <int DPL, bool EXT, class Eval>
-__device__ void run_chain(const SamplerArgs& A, Eval& ev, int64_t chain, double* S_arr)
+__device__ __forceinline__ void run_chain(const SamplerArgs& A, Eval& ev, int64_t chain, double* S_arr)
 {
     const int l = lane();
     const int D = A.data.D;

@@ -48,7 +48,10 @@ def _functions(obj, tmp):
     return funcs
 
 
-@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no llvm-objdump")
+needs_objdump = pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no llvm-objdump")
+
+
+@needs_objdump
 def test_buffer_resources_are_uniform(tmp_path):
     # a buffer access from a resource that differs between the lanes becomes a
     # loop over the distinct resources (the lanes narrowed, the access, the
@@ -69,3 +72,21 @@ def test_buffer_resources_are_uniform(tmp_path):
                         loops.append((name, text))
     assert seen == 22  # every instantiation: 11 shapes, with and without the optional features
     assert not loops, loops[:4]
+
+
+@needs_objdump
+def test_evaluators_stay_in_registers(tmp_path):
+    # a function that takes an evaluator by reference and is not inlined keeps
+    # it in scratch memory for the whole chain
+    kernels, others = 0, []
+    for obj in _device_objects(nuts.LIB_PATH):
+        if b"sampler_hmm_kernel" not in obj and b"sampler_wave_kernel" not in obj and \
+                b"sampler_grid_kernel" not in obj and b"sampler_team_kernel" not in obj and \
+                b"sampler_batch_kernel" not in obj:
+            continue
+        for name in _functions(obj, str(tmp_path)):
+            kernels += "_kernel" in name
+            if re.search(r"(Hmm|Wave|Grid|Batch)Eval", name):
+                others.append(name)
+    assert kernels > 100
+    assert not others, others
