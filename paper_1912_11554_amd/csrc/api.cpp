@@ -968,7 +968,7 @@ int nuts_sample_data(nuts_handle* h, const nuts_data* d, uint32_t flags, double 
     probe.uturn_gen = (flags & NUTS_UTURN_GENERALIZED) ? 1 : 0;
     probe.sub_merge = sub_merge;
     const bool extended = sampler_extended(probe);
-    GridPlan grid_plan{0, 0, 0};
+    GridPlan grid_plan{};
     if (path == NUTS_PATH_AUTO) {
         // many chains on a large shared fp32 data set: the matrix-core batch;
         // else the chains side by side on the grid path, each on its share of

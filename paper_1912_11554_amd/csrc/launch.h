@@ -178,6 +178,7 @@ struct GridPlan {
     int groups;  // per chain; 0: the tree state does not fit a CU's LDS
     int chains;  // per launch
     int team;    // row tiles a group holds in LDS (sampler_team_kernel), or 0: the rows stream from memory
+    double us;   // what an evaluation of every chain is expected to take, in microseconds
 };
 // `at_launch` (optional): an event recorded right before the sampler kernel,
 // after the set-up kernel.

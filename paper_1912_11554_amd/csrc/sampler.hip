@@ -57,30 +57,43 @@ hipError_t launch_sampler_wave(const SamplerArgs& a, hipStream_t stream)
 
 namespace {
 
-// What an evaluation takes, in microseconds, from runs of both paths over N =
-// 60 to 100,000 rows, D = 3 to 60 and 1 to 2,500 chains.
+// What an evaluation takes, in microseconds, fitted to runs of the paths over N
+// = 800 to 200,000 rows, D = 4 to 300 and 1 to 600 chains (within 15 %, the
+// streaming kernel at 17 to 32 columns within 30 %).
 //  - The wave path: 1.5 for the tree step and the reductions, and per 64 rows
-//    what the lanes of a row repeat of its row terms (0.3 fp64, 0.2 fp32 with
-//    one lane a row; 1.5, 1.1 with four; 3.7, 1.5 with eight).
-//  - A team: 1.7 (3.7 with an exchange between groups) and 0.35 a round of
-//    tiles over a group's workers.
-//  - The streaming grid kernel: 5, and per 64 rows of a group about a quarter
-//    of the wave path's (its fp64 rows of 16 slots spill: 0.35).
+//    what the lanes of a row repeat of its row terms, the rows in LDS or
+//    streamed.
+//  - A team: a step on a lone group or with an exchange between groups, and a
+//    round of tiles over a group's workers.
+//  - The streaming grid kernel: a step, and 64 rows of a group.  Rows beyond the
+//    caches are read from memory at 6.3 TB/s, once for all the chains of a
+//    launch, which go through them at the same pace.
 struct PathCost {
-    double wave_tile, stream_tile;
+    double wave_lds, wave_stream, team_lone, team_exchange, team_round, stream_step, stream_tile;
 };
 PathCost path_cost(const DataView& dv)
 {
-    const bool f64 = dv.dtype == NUTS_F64;
-    if (dv.split == 1) return {f64 ? 0.3 : 0.2, dv.cols == 16 ? 0.35 : 0.1};
-    if (dv.split == 4) return {f64 ? 1.5 : 1.1, f64 ? 0.5 : 0.25};
-    return {f64 ? 3.7 : 1.5, f64 ? 0.9 : 0.4};
+    static const PathCost f64[] = {{0.23, 0.32, 1.3, 3.4, 0.52, 4.7, 0.07}, {0.31, 0.39, 1.6, 4.0, 0.42, 9.6, 0.13},
+                                   {1.25, 3.4, 1.9, 4.7, 0.25, 4.5, 0.8},   {3.4, 3.5, 2.2, 5.0, 0.4, 5.1, 0.83},
+                                   {0, 0, 0, 0, 0, 7.5, 1.4},               {0, 0, 0, 0, 0, 8.0, 2.9},
+                                   {0, 0, 0, 0, 0, 11.0, 3.2}};
+    static const PathCost f32[] = {{0.14, 0.19, 1.4, 3.5, 0.24, 4.5, 0.034}, {0.21, 0.74, 1.4, 3.7, 0.33, 7.6, 0.083},
+                                   {0.55, 2.0, 1.8, 4.1, 0.42, 4.6, 0.4},    {1.7, 2.45, 2.1, 5.0, 0.4, 4.6, 0.4},
+                                   {0, 0, 0, 0, 0, 7.0, 0.7},                {0, 0, 0, 0, 0, 8.0, 1.4},
+                                   {0, 0, 0, 0, 0, 10.7, 1.7}};
+    const int D = dv.D;  // up to 8, 16, 32, 64, 128, 256 columns, and beyond
+    const int c = D <= 8 ? 0 : D <= 16 ? 1 : D <= 32 ? 2 : D <= 64 ? 3 : D <= 128 ? 4 : D <= 256 ? 5 : 6;
+    return dv.dtype == NUTS_F64 ? f64[c] : f32[c];
 }
+constexpr double kCachedBytes = 200e6;     // of the 256 MB cache beside the memory
+constexpr double kStreamBytesPerUs = 6.3e6;
 double launches(int64_t chains, int64_t per_launch) { return (double)((chains + per_launch - 1) / per_launch); }
-double team_cost(const GridPlan& p, int64_t chains)
+GridPlan team_plan(const DataView& dv, int64_t num_chains, int64_t groups, int64_t chains, int64_t tiles)
 {
-    const int rounds = (p.team + kTeamWaves - 2) / (kTeamWaves - 1);
-    return launches(chains, p.chains) * ((p.groups == 1 ? 1.7 : 3.7) + 0.35 * rounds);
+    const PathCost pc = path_cost(dv);
+    const int64_t rounds = (tiles + kTeamWaves - 2) / (kTeamWaves - 1);
+    const double step = (groups == 1 ? pc.team_lone : pc.team_exchange) + pc.team_round * (double)rounds;
+    return GridPlan{(int)groups, (int)chains, (int)tiles, launches(num_chains, chains) * step};
 }
 
 // The team for these chains: as many at a time as the groups that hold a
@@ -90,35 +103,59 @@ GridPlan plan_team(const DataView& dv, int max_depth, int sub_merge, int64_t num
     constexpr int kWorkers = kTeamWaves - 1;
     const size_t used = grid_resident_offset(dv.D, max_depth, sub_merge) +
                         sizeof(sampler::GridShared<1, kTeamWaves>) + 64;
-    if (used >= sampler::kMaxGroupLds) return GridPlan{0, 0, 0};
+    if (used >= sampler::kMaxGroupLds) return GridPlan{};
     const int64_t nt = (dv.N + 63) / 64;
     const int64_t cap = (int64_t)((sampler::kMaxGroupLds - used) / team_tile_bytes(dv.dtype, dv.D));  // tiles a group
-    if (cap < 1) return GridPlan{0, 0, 0};
+    if (cap < 1) return GridPlan{};
     const int64_t lone = kWorkers * (dv.dtype == NUTS_F64 ? kTeamLoneRounds64 : kTeamLoneRounds32);
-    if (nt <= lone && nt <= cap) return GridPlan{1, (int)std::min<int64_t>(num_chains, num_cu), (int)nt};
+    if (nt <= lone && nt <= cap) return team_plan(dv, num_chains, 1, std::min<int64_t>(num_chains, num_cu), nt);
     const int64_t fit = (nt + cap - 1) / cap;  // the fewest groups that hold the rows
-    if (fit > num_cu) return GridPlan{0, 0, 0};
+    if (fit > num_cu) return GridPlan{};
     // launches of equal size
     const int64_t most = std::min<int64_t>(num_chains, num_cu / fit);
     const int64_t n = (num_chains + most - 1) / most;
     const int64_t chains = (num_chains + n - 1) / n;
     const int64_t per_group = std::min<int64_t>(cap, kWorkers);
     const int64_t groups = std::min<int64_t>(num_cu / chains, std::max(fit, (nt + per_group - 1) / per_group));
-    return GridPlan{(int)groups, (int)chains, (int)((nt + groups - 1) / groups)};
+    return team_plan(dv, num_chains, groups, chains, (nt + groups - 1) / groups);
+}
+
+// The streaming launches of these chains.  Chains on one group each leave CUs
+// idle unless they are as many, and a last launch of few chains takes as long as
+// a full one: fewer chains at a time on more groups each can be ahead (130
+// chains on 1,000,000 x 100 fp64, ms a step: 23.3 all at once, 15.8 in two
+// launches, 13.3 in ten, 15.3 in 26, 18.3 one after another; on 20,000 x 300
+// 0.95, 0.66, 0.70, 1.15 and 2.54).  Fewer only where the gain is 4 %: the more
+// chains a launch has, the more they share of what they read.
+GridPlan plan_stream(const DataView& dv, int64_t num_chains, int num_cu)
+{
+    const PathCost pc = path_cost(dv);
+    const double tiles = (double)((dv.N + 63) / 64);
+    const double bytes = (double)dv.N * dv.D * (dv.dtype == NUTS_F64 ? 8.0 : 4.0);
+    const double memory = bytes > kCachedBytes ? bytes / kStreamBytesPerUs : 0.0;
+    // no more groups than the rows' blocks give work; and a group gathers the
+    // partials of its used columns in one pass of its worker lanes: ceil((D +
+    // 1) / groups) * groups <= D + groups slots
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>((dv.nb + kGridWaves - 2) / (kGridWaves - 1),
+                                                               (int64_t)(kGridWaves - 1) * kWave - dv.D));
+    GridPlan best{};
+    for (int64_t chains = std::min<int64_t>(num_chains, num_cu); chains >= 1; --chains) {
+        const int64_t groups = std::min<int64_t>(num_cu / chains, most);
+        const double step = std::max(pc.stream_step + pc.stream_tile * tiles / (double)groups, memory);
+        const double us = launches(num_chains, chains) * step;
+        if (best.groups == 0 || us < 0.96 * best.us) best = GridPlan{(int)groups, (int)chains, 0, us};
+    }
+    return best;
 }
 
 }  // namespace
 
 GridPlan plan_grid_sampler(const DataView& dv, int max_depth, int sub_merge, int64_t num_chains, int num_cu)
 {
-    const int chains = (int)std::min<int64_t>(num_chains, num_cu);
-    int64_t groups = num_cu / chains;  // streaming: the device shared out to the chains
-    groups = std::max<int64_t>(1, std::min<int64_t>(groups, (dv.nb + kGridWaves - 2) / (kGridWaves - 1)));
+    const GridPlan stream = plan_stream(dv, num_chains, num_cu);
     if (dv.D <= kWave) {
         const GridPlan team = plan_team(dv, max_depth, sub_merge, num_chains, num_cu);
-        const double stream = launches(num_chains, chains) *
-                              (5.0 + path_cost(dv).stream_tile * (double)((dv.N + 63) / 64) / (double)groups);
-        if (team.team > 0 && team_cost(team, num_chains) < stream) return team;
+        if (team.groups > 0 && team.us < stream.us) return team;
     }
     const void* k = pick_grid_kernel(dv, sub_merge != 0);
     int per_cu = 0;
@@ -126,25 +163,18 @@ GridPlan plan_grid_sampler(const DataView& dv, int max_depth, int sub_merge, int
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kGridWaves * kWave, lds) != hipSuccess)
         per_cu = 1;
     else if (per_cu < 1)
-        return GridPlan{0, 0, 0};  // the group's LDS does not fit a CU
-    // a group gathers the partials of its used columns in one pass of its
-    // worker lanes: ceil((D + 1) / groups) * groups <= D + groups slots
-    groups = std::min<int64_t>(groups, (int64_t)(kGridWaves - 1) * kWave - dv.D);
-    return GridPlan{(int)groups, chains, 0};
+        return GridPlan{};  // the group's LDS does not fit a CU
+    return stream;
 }
 
-// A streaming launch and the wave path read the rows at the same rate per CU,
-// so the grid path is ahead while the chains leave the wave path's slots empty
-// (4 chains on 100,000 x 50 fp64: 24 us an evaluation against 7,400).
 bool grid_beats_wave(const SamplerArgs& a, const GridPlan& plan, int num_cu)
 {
     if (plan.groups == 0) return false;
-    if (plan.team == 0) return a.num_chains <= num_cu;
     const int cpg = wave_path_resident(a);
     const int64_t slots = (int64_t)num_cu * (cpg > 0 ? cpg : 12);
-    const double wave =
-        launches(a.num_chains, slots) * (1.5 + (double)((a.data.N + 63) / 64) * path_cost(a.data).wave_tile);
-    return team_cost(plan, a.num_chains) < wave;
+    const PathCost pc = path_cost(a.data);
+    const double tile = cpg > 0 ? pc.wave_lds : pc.wave_stream;
+    return plan.us < launches(a.num_chains, slots) * (1.5 + tile * (double)((a.data.N + 63) / 64));
 }
 
 hipError_t launch_sampler_grid(const SamplerArgs& a, const GridPlan& plan, double* partials, double* result,

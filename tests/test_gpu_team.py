@@ -71,7 +71,8 @@ def test_wide_data_of_their_own_is_refused(sampler):
 
 # launches of fewer chains than the call has: shared rows that need several
 # groups a chain; and wide rows, which stream, side by side
-@pytest.mark.parametrize("C,N,D", [(12, 20000, 25), (150, 3000, 10), (9, 1500, 100)])
+@pytest.mark.parametrize("C,N,D", [(12, 20000, 25), (150, 3000, 10), (9, 1500, 100), (130, 4000, 70),
+                                   (257, 2000, 130)])
 def test_chains_over_several_launches(sampler, orc, C, N, D):
     X, y, _ = workloads.make_logistic(N, D, w_scale=0.8 / np.sqrt(D), key=[72, 1000 * N + D])
     kw = dict(step_size=0.5 / np.sqrt(0.2 * N + 1), max_tree_depth=5, num_warmup=0, num_samples=4)
@@ -79,6 +80,27 @@ def test_chains_over_several_launches(sampler, orc, C, N, D):
     r = sampler.sample(X, y, num_chains=C, seed=23, **kw)
     _check(orc, X, y, r, sorted({0, C // 2 - 1, C // 2, C - 1}), 23, **kw)
     assert r["grad_evals"] == int(r["stats"]["num_steps"].sum()) + C
+
+
+# wide rows beyond the caches: chains that share the device take no longer than
+# the same chains one after another (a lone chain's step reads all the rows at
+# the memory's rate; 130 at once on one group each took 1.15 times as long)
+def test_many_wide_chains_no_slower_than_in_turn(sampler):
+    import torch
+    N, D, C = 500000, 200, 130
+    g = torch.Generator(device="cuda").manual_seed(1)
+    X = torch.randn(N, D, generator=g, device="cuda", dtype=torch.float64)
+    y = (torch.rand(N, generator=g, device="cuda") < 0.5).to(torch.uint8)
+    say("wide chains in turn", N, D, C)
+    d = sampler.data(X, y)
+    del X
+    us = {}
+    for c in (1, 1, C):  # (the first call loads the kernel)
+        r = d.sample(step_size=1e-7, max_tree_depth=3, num_warmup=0, num_samples=4, num_chains=c, seed=1,
+                     time_kernel=True)
+        us[c] = 1e3 * r["kernel_ms"] / r["grad_evals"]
+    d.free()
+    assert us[C] < us[1], us
 
 
 @pytest.mark.parametrize("extra", [dict(uturn_generalized=True), dict(subtree_merge=True),
