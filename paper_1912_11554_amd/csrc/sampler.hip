@@ -85,6 +85,7 @@ PathCost path_cost(const DataView& dv)
     const int c = D <= 8 ? 0 : D <= 16 ? 1 : D <= 32 ? 2 : D <= 64 ? 3 : D <= 128 ? 4 : D <= 256 ? 5 : 6;
     return dv.dtype == NUTS_F64 ? f64[c] : f32[c];
 }
+constexpr int64_t kMaxLaunchChains = 1 << 20;  // lone groups a launch
 constexpr double kCachedBytes = 200e6;     // of the 256 MB cache beside the memory
 constexpr double kStreamBytesPerUs = 6.3e6;
 double launches(int64_t chains, int64_t per_launch) { return (double)((chains + per_launch - 1) / per_launch); }
@@ -108,7 +109,13 @@ GridPlan plan_team(const DataView& dv, int max_depth, int sub_merge, int64_t num
     const int64_t cap = (int64_t)((sampler::kMaxGroupLds - used) / team_tile_bytes(dv.dtype, dv.D));  // tiles a group
     if (cap < 1) return GridPlan{};
     const int64_t lone = kWorkers * (dv.dtype == NUTS_F64 ? kTeamLoneRounds64 : kTeamLoneRounds32);
-    if (nt <= lone && nt <= cap) return team_plan(dv, num_chains, 1, std::min<int64_t>(num_chains, num_cu), nt);
+    if (nt <= lone && nt <= cap) {
+        // lone groups wait for no other: one launch of all chains, a CU taking
+        // the next chain when it is done with one
+        GridPlan p = team_plan(dv, num_chains, 1, num_cu, nt);
+        p.chains = (int)std::min<int64_t>(num_chains, kMaxLaunchChains);
+        return p;
+    }
     const int64_t fit = (nt + cap - 1) / cap;  // the fewest groups that hold the rows
     if (fit > num_cu) return GridPlan{};
     // launches of equal size
