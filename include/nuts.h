@@ -149,15 +149,18 @@ int nuts_data_potential_grad_noalloc(nuts_handle* h, const nuts_data* d, double 
 
 /* The same quantities for K positions on shared fp32 data, computed as one
  * contraction: E = X W^T (N x D by D x K) and G = X^T R (D x N by N x K) on
- * the fp32 matrix cores, with R = sigmoid(E) - y elementwise (the batched
+ * the matrix cores, with R = sigmoid(E) - y elementwise (the batched
  * form of the gradient in Section 3.1's vectorized setting).  X and W enter
  * the products as fp32 (W is rounded to fp32 for the likelihood terms; the
- * prior uses W in fp64), products accumulate in fp32 per row range, and the
+ * prior uses W in fp64), each factor as three bf16 parts (exact for magnitudes
+ * of 2^-110 and more, off by at most 2^-134 below), products accumulate in fp32
+ * per row range, and the
  * per-position sums of the loss and of the partial rows are fp64.  Relative
  * error versus fp64 arithmetic on the same fp32 X is ~1e-6.  NUTS_EUNSUPPORTED
  * for fp64 data, per-chain data or D > 132.  The first call on a data set
  * builds a second device copy of X in the row-stage layout this path reads
- * (kept until nuts_data_free). */
+ * (84, 212, 404 or 788 bytes a row for up to 4, 36, 68 or 132 columns; kept
+ * until nuts_data_free). */
 int nuts_data_potential_grad_batched(nuts_handle* h, const nuts_data* d, double prior_scale,
                                      const double* W, int64_t K, double* out_U, double* out_grad);
 

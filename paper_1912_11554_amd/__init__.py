@@ -344,7 +344,7 @@ class Data:
     def potential_grad(self, W, prior_scale=1.0, out_U=None, out_grad=None, batched=False,
                        no_alloc=False):
         """U [K] and grad [K, D] at positions W [K, D] (numpy or device tensor).
-        batched=True uses nuts_data_potential_grad_batched (fp32 matrix cores).
+        batched=True uses nuts_data_potential_grad_batched (matrix cores).
         no_alloc=True uses nuts_data_potential_grad_noalloc: W, out_U and
         out_grad must then be device tensors, and the call returns once the
         work is enqueued on the handle's stream (synchronise before reading)."""

@@ -22,10 +22,11 @@
 // rounded after every four).  Against 64-bit arithmetic the gradient of 256
 // positions on 200,000 x 129 is off by 7.4e-7 (8.5e-7 with the fp32
 // instruction), the log-likelihood of 500 draws over 581,012 x 55 by 2.1e-9
-// (2.2e-9).  256 positions on 200,000 x 129 take 187 us a call, from 264; the
-// loop waits for LDS (six reads of every element per wave and pass, about as
-// many cycles as the products) and the matrix cores in turn: reading the next
-// step's operands ahead of the current products changed nothing, and holding the
+// (2.2e-9).  256 positions on 200,000 x 129 take 181 to 185 us a call, from 264.
+// Of the pass's cycles the matrix cores are busy in 45 %, the vector ALUs with
+// other instructions in 42 %, LDS in 31 % (six reads of every element a wave, no
+// bank conflict), with two waves a SIMD to overlap them: reading the next step's
+// operands ahead of the current products changed nothing, and holding the
 // corrections to the finite range costs 5 to 7 %.
 //
 // v_mfma_f32_16x16x32_bf16: lane l gives A[l % 16][8 (l / 16) + i] and

@@ -358,7 +358,7 @@ hipError_t launch_batch_potential(const BatchView& bv, double prior_scale, const
 }
 
 // ---------------------------------------------------------------------------
-// Log-likelihood over a batch of draws (fp32 matrix cores): one pass over X
+// Log-likelihood over a batch of draws (bf16 matrix cores): one pass over X
 // per tile of 128 draws computing E = X W^T, then per draw the negative log
 // likelihood summed in fp64 (partial rows per group, added in group order by
 // the finish kernel), and optionally per row the sum of sigmoid(eta) over

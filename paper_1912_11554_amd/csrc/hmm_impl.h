@@ -677,7 +677,9 @@ struct HmmEval {
 // registers, the occupancies most of 16 KB of LDS.  With the prefix and the
 // suffix both as matrix products over the lanes, every product rescaled and
 // every step normalised, the four-chain form took 6.92 ms.  What bounds it is
-// the chain of dependent fp64 instructions and LDS shuffles of one evaluation.
+// the chain of dependent fp64 instructions and LDS shuffles of one evaluation:
+// the vector ALUs issue in 61 % of the cycles, LDS is busy in 45 %, at 1.8 waves
+// a SIMD.
 // With the optional features (adapted step size) one chain takes 7.1 us an
 // evaluation with two states, 9.7 with three and 12.0 with four; as four chains
 // a group, rescaled at every product, 8.1, 11.9 and 18.6.

@@ -35,10 +35,13 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 KERNEL_UNITS = {
     "potential_grad_kernel": ("potential.hip",),
     "potential_items_kernel": ("potential.hip",),
+    "potential_rows_kernel": ("potential.hip",),
     "sampler_grid_kernel": ("sampler.hip", "sampler_f32.hip", "sampler_f64.hip", "sampler_ext_f32.hip",
                             "sampler_ext_f64.hip"),
     "sampler_wave_kernel": ("sampler.hip", "sampler_f32.hip", "sampler_f64.hip", "sampler_ext_f32.hip",
                             "sampler_ext_f64.hip"),
+    "sampler_team_kernel": ("sampler.hip", "team_f32.hip", "team_f64.hip", "team_ext_f32.hip",
+                            "team_ext_f64.hip"),
     "sampler_batch_kernel": ("batch.hip",),
     "batch_pass_kernel": ("batch.hip",),
     "batch_ll_kernel": ("batch.hip",),
