@@ -159,7 +159,7 @@ int nuts_data_potential_grad_noalloc(nuts_handle* h, const nuts_data* d, double 
  * error versus fp64 arithmetic on the same fp32 X is ~1e-6.  NUTS_EUNSUPPORTED
  * for fp64 data, per-chain data or D > 132.  The first call on a data set
  * builds a second device copy of X in the row-stage layout this path reads
- * (84, 212, 404 or 788 bytes a row for up to 4, 36, 68 or 132 columns; kept
+ * (20, 212, 404 or 788 bytes a row for up to 4, 36, 68 or 132 columns; kept
  * until nuts_data_free). */
 int nuts_data_potential_grad_batched(nuts_handle* h, const nuts_data* d, double prior_scale,
                                      const double* W, int64_t K, double* out_U, double* out_grad);

@@ -66,8 +66,8 @@ namespace {
 //  - A team: a step on a lone group or with an exchange between groups, and a
 //    round of tiles over a group's workers.
 //  - The streaming grid kernel: a step, and 64 rows of a group.  Rows beyond the
-//    caches are read from memory at 6.3 TB/s, once for all the chains of a
-//    launch, which go through them at the same pace.
+//    caches are read from memory at 6.3 TB/s, shared ones once for all the
+//    chains of a launch, which go through them at the same pace.
 struct PathCost {
     double wave_lds, wave_stream, team_lone, team_exchange, team_round, stream_step, stream_tile;
 };
@@ -138,8 +138,7 @@ GridPlan plan_stream(const DataView& dv, int64_t num_chains, int num_cu)
 {
     const PathCost pc = path_cost(dv);
     const double tiles = (double)((dv.N + 63) / 64);
-    const double bytes = (double)dv.N * dv.D * (dv.dtype == NUTS_F64 ? 8.0 : 4.0);
-    const double memory = bytes > kCachedBytes ? bytes / kStreamBytesPerUs : 0.0;
+    const double set_bytes = (double)dv.N * dv.D * (dv.dtype == NUTS_F64 ? 8.0 : 4.0);
     // no more groups than the rows' blocks give work; and a group gathers the
     // partials of its used columns in one pass of its worker lanes: ceil((D +
     // 1) / groups) * groups <= D + groups slots
@@ -148,6 +147,8 @@ GridPlan plan_stream(const DataView& dv, int64_t num_chains, int num_cu)
     GridPlan best{};
     for (int64_t chains = std::min<int64_t>(num_chains, num_cu); chains >= 1; --chains) {
         const int64_t groups = std::min<int64_t>(num_cu / chains, most);
+        const double bytes = set_bytes * (dv.nds > 1 ? (double)chains : 1.0);  // a launch's rows
+        const double memory = bytes > kCachedBytes ? bytes / kStreamBytesPerUs : 0.0;
         const double step = std::max(pc.stream_step + pc.stream_tile * tiles / (double)groups, memory);
         const double us = launches(num_chains, chains) * step;
         if (best.groups == 0 || us < 0.96 * best.us) best = GridPlan{(int)groups, (int)chains, 0, us};
