@@ -58,29 +58,35 @@ hipError_t launch_sampler_wave(const SamplerArgs& a, hipStream_t stream)
 namespace {
 
 // What an evaluation takes, in microseconds, fitted to runs of the paths over N
-// = 800 to 200,000 rows, D = 4 to 300 and 1 to 600 chains (within 15 %, the
+// = 1 to 200,000 rows, D = 1 to 300 and 1 to 600 chains (within 15 %, the
 // streaming kernel at 17 to 32 columns within 30 %).
-//  - The wave path: 1.5 for the tree step and the reductions, and per 64 rows
-//    what the lanes of a row repeat of its row terms, the rows in LDS or
-//    streamed.
-//  - A team: a step on a lone group or with an exchange between groups, and a
-//    round of tiles over a group's workers.
+//  - The wave path: the tree step and the reductions, and per 64 rows (of its
+//    row blocks) what the lanes of a row repeat of its row terms, the rows in
+//    LDS or streamed.
+//  - A team on a lone group: the first round of tiles over its workers, and
+//    as many more tiles; with an exchange between groups a step and a round.
 //  - The streaming grid kernel: a step, and 64 rows of a group.  Rows beyond the
 //    caches are read from memory at 6.3 TB/s, shared ones once for all the
 //    chains of a launch, which go through them at the same pace.
 struct PathCost {
-    double wave_lds, wave_stream, team_lone, team_exchange, team_round, stream_step, stream_tile;
+    double wave_step, wave_lds, wave_stream, lone_first, lone_round, team_step, team_round, stream_step, stream_tile;
 };
 PathCost path_cost(const DataView& dv)
 {
-    static const PathCost f64[] = {{0.23, 0.32, 1.3, 3.4, 0.52, 4.7, 0.07}, {0.31, 0.39, 1.6, 4.0, 0.42, 9.6, 0.13},
-                                   {1.25, 3.4, 1.9, 4.7, 0.25, 4.5, 0.8},   {3.4, 3.5, 2.2, 5.0, 0.4, 5.1, 0.83},
-                                   {0, 0, 0, 0, 0, 7.5, 1.4},               {0, 0, 0, 0, 0, 8.0, 2.9},
-                                   {0, 0, 0, 0, 0, 11.0, 3.2}};
-    static const PathCost f32[] = {{0.14, 0.19, 1.4, 3.5, 0.24, 4.5, 0.034}, {0.21, 0.74, 1.4, 3.7, 0.33, 7.6, 0.083},
-                                   {0.55, 2.0, 1.8, 4.1, 0.42, 4.6, 0.4},    {1.7, 2.45, 2.1, 5.0, 0.4, 4.6, 0.4},
-                                   {0, 0, 0, 0, 0, 7.0, 0.7},                {0, 0, 0, 0, 0, 8.0, 1.4},
-                                   {0, 0, 0, 0, 0, 10.7, 1.7}};
+    static const PathCost f64[] = {{1.36, 0.22, 0.32, 1.6, 0.62, 3.4, 0.52, 4.7, 0.07},
+                                   {1.62, 0.27, 0.39, 1.58, 0.9, 4.0, 0.42, 9.6, 0.13},
+                                   {1.34, 1.3, 3.4, 1.8, 1.1, 4.7, 0.25, 4.5, 0.72},
+                                   {1.3, 2.7, 3.5, 2.15, 1.1, 5.0, 0.4, 5.1, 0.83},
+                                   {0, 0, 0, 0, 0, 0, 0, 7.5, 1.4},
+                                   {0, 0, 0, 0, 0, 0, 0, 8.0, 2.9},
+                                   {0, 0, 0, 0, 0, 0, 0, 11.0, 3.2}};
+    static const PathCost f32[] = {{1.3, 0.135, 0.19, 1.46, 0.28, 3.5, 0.24, 4.5, 0.034},
+                                   {1.62, 0.17, 0.74, 1.5, 0.42, 3.7, 0.33, 7.6, 0.083},
+                                   {1.48, 0.57, 2.0, 1.65, 0.95, 4.1, 0.42, 4.6, 0.37},
+                                   {1.4, 1.16, 2.45, 2.1, 0.9, 5.0, 0.4, 4.6, 0.4},
+                                   {0, 0, 0, 0, 0, 0, 0, 7.0, 0.7},
+                                   {0, 0, 0, 0, 0, 0, 0, 8.0, 1.4},
+                                   {0, 0, 0, 0, 0, 0, 0, 10.7, 1.7}};
     const int D = dv.D;  // up to 8, 16, 32, 64, 128, 256 columns, and beyond
     const int c = D <= 8 ? 0 : D <= 16 ? 1 : D <= 32 ? 2 : D <= 64 ? 3 : D <= 128 ? 4 : D <= 256 ? 5 : 6;
     return dv.dtype == NUTS_F64 ? f64[c] : f32[c];
@@ -92,8 +98,10 @@ double launches(int64_t chains, int64_t per_launch) { return (double)((chains + 
 GridPlan team_plan(const DataView& dv, int64_t num_chains, int64_t groups, int64_t chains, int64_t tiles)
 {
     const PathCost pc = path_cost(dv);
-    const int64_t rounds = (tiles + kTeamWaves - 2) / (kTeamWaves - 1);
-    const double step = (groups == 1 ? pc.team_lone : pc.team_exchange) + pc.team_round * (double)rounds;
+    constexpr int64_t kWorkers = kTeamWaves - 1;
+    const double step = groups == 1
+                            ? pc.lone_first + pc.lone_round * (double)std::max<int64_t>(tiles - kWorkers, 0) / kWorkers
+                            : pc.team_step + pc.team_round * (double)((tiles + kWorkers - 1) / kWorkers);
     return GridPlan{(int)groups, (int)chains, (int)tiles, launches(num_chains, chains) * step};
 }
 
@@ -182,7 +190,11 @@ bool grid_beats_wave(const SamplerArgs& a, const GridPlan& plan, int num_cu)
     const int64_t slots = (int64_t)num_cu * (cpg > 0 ? cpg : 12);
     const PathCost pc = path_cost(a.data);
     const double tile = cpg > 0 ? pc.wave_lds : pc.wave_stream;
-    return plan.us < launches(a.num_chains, slots) * (1.5 + tile * (double)((a.data.N + 63) / 64));
+    // (by its blocks: a few rows do not cost it 64)
+    const double tiles = (double)(a.data.nb * rows_per_block(a.data)) / 64.0;
+    // (level: the wave path, which fills no LDS of its own before the first step
+    // and exchanges nothing)
+    return plan.us < 0.95 * launches(a.num_chains, slots) * (pc.wave_step + tile * tiles);
 }
 
 hipError_t launch_sampler_grid(const SamplerArgs& a, const GridPlan& plan, double* partials, double* result,
